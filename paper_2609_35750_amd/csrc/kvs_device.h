@@ -164,11 +164,14 @@ __device__ __forceinline__ void dma_b32(const void* base, uint32_t off, uint32_t
       : "memory");
 }
 // Asynchronous copy of 16 bytes from this lane's own global address to LDS
-// byte address lds + 16 l (gathers whose rows have no common base).
+// byte address lds + 16 l (gathers whose rows have no common base).  Read as a
+// stream (nt): each byte is used by one wave, so keeping it in the caches only
+// displaces other waves' lines.  The 64-rollout decode (1.07 GB of K and V,
+// D = 128) went from 5.6 to 6.4 TB/s with it, 193 -> 167 us.
 __device__ __forceinline__ void dma_b128_global(const void* src, uint32_t lds) {
   uint32_t saved;
   asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt\n\ts_mov_b32 m0, %0"
       : "=&s"(saved)
       : "v"(src), "s"(lds)
       : "memory");
