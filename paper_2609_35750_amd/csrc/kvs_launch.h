@@ -70,8 +70,8 @@ struct PagedDecode {
   void* ws;
   hipStream_t stream;
 };
-int paged_nsplit(int S, int Hkv, int max_blocks, int BS, int D);
-size_t paged_ws_bytes(int S, int Hq, int D, int nsplit);
+int paged_units(int S, int Hkv, int max_blocks, int BS, int D);
+size_t paged_ws_bytes(int S, int Hq, int D, int units);
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,
                                void* vc, int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
 hipError_t launch_paged_evict(const int* slots, int n, int* slot_pos, int num_slots, hipStream_t stream);

@@ -10,7 +10,8 @@
 // block * block_size + row), or -1 (empty or evicted).  A sequence's blocks are
 // listed in its row of the block table.
 //
-// Decode: one wave per (sequence, KV head, split).  The wave walks its split's
+// Decode: one wave per (sequence, KV head, split); how many splits a sequence
+// gets follows from its blocks (decode_unit).  The wave walks its split's
 // cache slots in tiles of 32, gathering each tile's K and V rows from their
 // blocks into LDS with asynchronous global-to-LDS copies (double-buffered, no
 // workgroup barrier: each wave owns its buffers), computes S^T = K Q^T with the
@@ -22,6 +23,7 @@
 #include "kvs_launch.h"
 
 #include <algorithm>
+#include <climits>
 
 namespace kvs {
 
@@ -64,9 +66,13 @@ struct DecodeArgs {
   const int* slot_pos;    // [num_blocks * BS]
   const int* table;       // [S][max_blocks]
   const int* nblk;        // [S]
-  float* part;            // [S][Hq][nsplit][D]: unnormalised O of each split (relative to its max)
-  float* part_ml;         // [S][Hq][nsplit][2]: max (log2 units), sum
-  int S, Hq, Hkv, G, max_blocks, BS, num_blocks, nsplit;
+  // rows of the partials: units * Hq, sequence s from seq_units[s].x * Hq on as [q-head][its units]
+  float* part;            // [rows][D]: unnormalised O of each split (relative to its max)
+  float2* part_ml;        // [rows]: max (log2 units), sum
+  int2* seq_units;        // [S]: first unit and number of units of the sequence
+  uint16_t* o;            // [S][Hq][D]: written here for sequences of one unit, by the merge for the others
+  float* lse;             // [S][Hq]
+  int S, Hq, Hkv, G, max_blocks, BS, num_blocks, units;
   float scale_log2;       // softmax_scale * log2(e)
 };
 
@@ -114,6 +120,123 @@ struct GatherStager {
   }
 };
 
+// The split of the decode's work.  A unit is a run of a sequence's 32-slot
+// tiles that one wave walks per KV head; every sequence gets at least one.
+// All sequences are cut with one size, the smallest C tiles for which the
+// units fit the grid (paged_units), so ragged sequences give equal waves and
+// a table wider than what it holds costs nothing.  Each wave finds its unit
+// by itself from seq_blocks (S <= kPlanSeqs: lanes hold the tile counts in
+// registers and C is searched by bisection; beyond, C = total / (units - S),
+// which always fits since sum ceil(t / C) <= total / C + S).
+// Cutting every sequence into the same number of splits instead: 24 rollouts
+// of 200 to 9,000 entries (D = 64, 195 MB) 51.8 -> 39.9 us, 40 of 500 to 8,000
+// (D = 128, 674 MB) 162 -> 119 us, one of 16,000 beside 63 of 200 379 -> 28 us
+// (these with the streamed gather); the plan itself adds 1 to 2 us to a wave.
+constexpr int kPlanRegs = 4, kPlanSeqs = kPlanRegs * kWave;
+// Least tiles of a unit.  A lone wave takes about 2 us a tile (one memory
+// latency), so small batches want many short units until the merge's reads
+// outweigh it: one rollout of 4,096 entries took 14.0 us with 4, 11.6 with 2.
+constexpr int kMinTiles = 2;
+
+struct DecodeUnit {
+  int s, nslots, first, n, chunk;   // sequence, its slots, its first unit, its units, this one among them
+};
+
+// Inclusive prefix sum over the 64 lanes (data-parallel moves: no LDS round trips).
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // last lane of rows 0, 2 to rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2, 3
+  return x;
+}
+__device__ __forceinline__ int wave_last(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
+
+constexpr int kTileCap = 1 << 22;   // tiles of one sequence the plan tells apart (134 M slots); exact in fp32
+// x / y for x >= 0, y >= 1: float quotient, corrected, where x is exact in fp32 (an integer division of the
+// compiler's is several times the dependent instructions, on every wave's way to its first load)
+__device__ __forceinline__ int quick_div(int x, int y) {
+  if (x > kTileCap) return x / y;
+  int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y));
+  const int r = x - q * y;
+  return q + (r >= y) - (r < 0);
+}
+// max(1, ceil(t / C)) for 0 <= t <= kTileCap, C >= 1, rcpC = 1 / C
+__device__ __forceinline__ int unit_count(int t, int C, float rcpC) {
+  int q = (int)((float)t * rcpC);
+  int r = t - q * C;
+  if (r < 0) --q, r += C;
+  if (r >= C) ++q, r -= C;
+  return max(1, q + (r > 0));
+}
+
+// The unit and KV head of workgroup `wg`; s = -1 past the last one.  All lanes
+// of the wave take part.  A sequence's workgroups are consecutive, its units
+// fastest, then the KV heads.
+__device__ __forceinline__ DecodeUnit decode_unit(const DecodeArgs& a, int wg, int lane, int& g) {
+  // slots of the blocks in use (clamped to the table width; some may be evicted)
+  auto slots_of = [&](int s) __attribute__((always_inline)) {
+    return s < a.S ? min(max(a.nblk[s], 0), a.max_blocks) * a.BS : 0;
+  };
+  auto tiles_of = [&](int ns) __attribute__((always_inline)) {
+    return (int)min(((unsigned)ns + kDecTile - 1) / kDecTile, (unsigned)kTileCap);
+  };
+  const int u = quick_div(wg, a.Hkv);
+  int t[kPlanRegs], C = INT_MAX / 2;
+  const int ns0 = slots_of(lane);
+  t[0] = tiles_of(ns0);
+#pragma unroll
+  for (int k = 1; k < kPlanRegs; ++k) t[k] = k * kWave < a.S ? tiles_of(slots_of(k * kWave + lane)) : 0;
+  if (a.S <= kPlanSeqs) {
+    // total <= 2^30: fits
+    const int total = wave_last(wave_scan(t[0] + t[1] + t[2] + t[3]));
+    auto units_at = [&](int c) __attribute__((always_inline)) {
+      const float rc = __builtin_amdgcn_rcpf((float)c);
+      int n = 0;
+#pragma unroll
+      for (int k = 0; k < kPlanRegs; ++k)
+        if (k * kWave < a.S) n += k * kWave + lane < a.S ? unit_count(t[k], c, rc) : 0;
+      return wave_last(wave_scan(n));
+    };
+    C = max(kMinTiles, quick_div(total - 1, a.units) + 1);   // ceil(total / units), 1 for 0
+    if (units_at(C) > a.units) {
+      int lo = C, hi = min(total, kTileCap);   // units_at(lo) > units >= S = units_at(hi)
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (units_at(mid) > a.units) lo = mid;
+        else hi = mid;
+      }
+      C = hi;
+    }
+  } else if (a.units > a.S) {
+    long long total = 0;   // below 2^53
+    for (int s0 = 0; s0 < a.S; s0 += kWave) total += wave_last(wave_scan(tiles_of(slots_of(s0 + lane))));
+    C = max(kMinTiles, (int)fmin((double)total / (a.units - a.S) + 1.0, (double)(INT_MAX / 2)));
+  }
+  const float rc = __builtin_amdgcn_rcpf((float)C);
+  int base = 0;
+  for (int s0 = 0; s0 < a.S; s0 += kWave) {
+    const int ns = s0 == 0 ? ns0 : slots_of(s0 + lane);
+    const int n = s0 + lane < a.S ? unit_count(tiles_of(ns), C, rc) : 0;
+    const int incl = wave_scan(n);
+    const unsigned long long hit = __ballot(u < base + incl);
+    if (hit != 0ull) {
+      const int l = __builtin_ctzll(hit);
+      const int nl = __builtin_amdgcn_readlane(n, l);
+      const int first = base + __builtin_amdgcn_readlane(incl, l) - nl;
+      const int rem = wg - first * a.Hkv;
+      g = __builtin_amdgcn_readfirstlane(quick_div(rem, nl));
+      const int chunk = rem - g * nl;
+      return {s0 + l, __builtin_amdgcn_readlane(ns, l), first, nl, chunk};
+    }
+    base += wave_last(incl);
+  }
+  g = 0;
+  return {-1, 0, 0, 0, 0};
+}
+
 // Copies in flight per wave: a ring of kDecRing tiles (K, V and the tile's
 // slot_pos values), one ahead of the one being computed.  D = 128 uses 37 KB
 // of LDS per wave, so four waves (one per SIMD) share a CU; D = 64 18 KB
@@ -148,22 +271,21 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
   __shared__ __attribute__((aligned(256))) int sTab[2][kWave];   // block-table entries of a tile's rows
   __shared__ __attribute__((aligned(256))) int sPos[R][kWave];   // slot_pos of a tile's rows
 
-  int wg = blockIdx.x;
-  const int sp = wg % a.nsplit;
-  wg /= a.nsplit;
-  const int g = wg % a.Hkv;
-  const int s = wg / a.Hkv;
   const int lane = threadIdx.x, half = lane >> 5, col = lane & 31;
+  int g;
+  const DecodeUnit du = decode_unit(a, blockIdx.x, lane, g);
+  if (du.s < 0) return;
+  const int s = du.s;
   const auto rl = Lay<D, true>::row_lane(lane);
   const int tl = Lay<D, true>::tr_lo(lane), th = Lay<D, true>::tr_hi(lane);
 
-  // blocks in use by sequence s (clamped to the table width; some slots may be evicted)
-  const int nslots = min(max(a.nblk[s], 0), a.max_blocks) * a.BS;
-  // the sequence's slots in nsplit equal ranges of whole tiles
-  const int per = ((nslots + a.nsplit - 1) / a.nsplit + kDecTile - 1) / kDecTile * kDecTile;
-  const int c_begin = min(sp * per, nslots);
-  const int c_end = min(c_begin + per, nslots);
-  const int ntile = c_end > c_begin ? (c_end - c_begin + kDecTile - 1) / kDecTile : 0;
+  const int nslots = du.nslots;
+  // the sequence's tiles in du.n equal runs
+  const int tiles = (int)(((unsigned)nslots + kDecTile - 1) / kDecTile);
+  const long long per = (long long)__builtin_amdgcn_readfirstlane(quick_div(tiles + du.n - 1, du.n)) * kDecTile;
+  const int c_begin = (int)min(du.chunk * per, (long long)nslots);
+  const int c_end = (int)min(c_begin + per, (long long)nslots);
+  const int ntile = c_end > c_begin ? (int)(((unsigned)(c_end - c_begin) + kDecTile - 1) / kDecTile) : 0;
 
   // Q^T operand: column n = q-head g * G + n of the group (zero for n >= G)
   const int hcol = g * a.G + col;
@@ -269,24 +391,34 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
     valid_q[R - 1] = 0u;
   }
 
-  // partial of this split for q-head column `col`
+  if (lane == 0 && g == 0 && du.chunk == 0) a.seq_units[s] = make_int2(du.first, du.n);
   const float l_tot = halves_sum(l_run);
-  if (col_ok) {
-    const size_t pidx = ((size_t)s * a.Hq + hcol) * a.nsplit + sp;
-    float* dst = a.part + pidx * D;
-    if (l_tot > 0.f) {   // an empty split leaves its O unwritten (the merge skips it)
+  if (!col_ok) return;
+  if (du.n == 1) {   // the sequence's only unit: O and LSE directly
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    uint16_t* orow = a.o + ((size_t)s * a.Hq + hcol) * D;
 #pragma unroll
-      for (int d = 0; d < DB; ++d)
+    for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          *reinterpret_cast<float4*>(dst + 32 * d + 8 * q4 + 4 * half) =
-              make_float4(acc[d][4 * q4], acc[d][4 * q4 + 1], acc[d][4 * q4 + 2], acc[d][4 * q4 + 3]);
-    }
-    if (half == 0) {
-      a.part_ml[2 * pidx] = m_run;
-      a.part_ml[2 * pidx + 1] = l_tot;
-    }
+      for (int q4 = 0; q4 < 4; ++q4)
+        *reinterpret_cast<uint2*>(orow + 32 * d + 8 * q4 + 4 * half) =
+            pack4_bf16(acc[d][4 * q4] * inv, acc[d][4 * q4 + 1] * inv, acc[d][4 * q4 + 2] * inv,
+                       acc[d][4 * q4 + 3] * inv);
+    if (half == 0) a.lse[(size_t)s * a.Hq + hcol] = l_tot > 0.f ? (m_run + __log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
+    return;
   }
+  // partial of this unit for q-head column `col`
+  const size_t pidx = (size_t)du.first * a.Hq + (size_t)hcol * du.n + du.chunk;
+  float* dst = a.part + pidx * D;
+  if (l_tot > 0.f) {   // an empty unit leaves its O unwritten (the merge skips it)
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *reinterpret_cast<float4*>(dst + 32 * d + 8 * q4 + 4 * half) =
+            make_float4(acc[d][4 * q4], acc[d][4 * q4 + 1], acc[d][4 * q4 + 2], acc[d][4 * q4 + 3]);
+  }
+  if (half == 0) a.part_ml[pidx] = make_float2(m_run, l_tot);
 }
 
 // Merge the splits of one (sequence, q-head): W waves.  The split weights
@@ -294,19 +426,28 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
 // LDS, then D / 4 lanes read one split's partial each as float4 and the
 // 64 W / (D / 4) groups of lanes take the splits in turn.  Bound by the
 // latency of its reads: one wave walking the splits in series took 71.6 us
-// for 32 rows of 128 splits (one 16,000-token rollout, 32 q-heads), this 7.1;
-// 8.7 -> 4.5 us for 576 rows of 11 splits.
-constexpr int kMaxSplit = 2048;   // splits per (sequence, KV head): one round of resident waves, see paged_nsplit
+// for 32 rows of 128 splits (one 16,000-token rollout, 32 q-heads), four waves
+// 7.1, sixteen with the first partials requested before the weights are known
+// about 4.5; 8.7 -> 4.5 us for 576 rows of 11 splits.
+constexpr int kMaxSplit = 2048;   // splits of one sequence: at most one round of resident waves, see paged_units
 template <int D, int W>
-__global__ void __launch_bounds__(64 * W) paged_combine_kernel(const float* __restrict__ part,
-                                                               const float* __restrict__ part_ml, int nsplit,
-                                                               uint16_t* __restrict__ o, float* __restrict__ lse) {
+__global__ void __launch_bounds__(64 * W) paged_combine_kernel(DecodeArgs a) {
   constexpr int LPS = D / 4, P = kWave * W / LPS;   // lanes per split, splits per pass
   __shared__ float sw[kMaxSplit];
   __shared__ float sred[2][W];
   __shared__ float4 sx[kWave * W];
   const int r = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
-  const float2* ml = reinterpret_cast<const float2*>(part_ml) + (size_t)r * nsplit;
+  const int2 su = a.seq_units[r / a.Hq];
+  const int nsplit = min(su.y, kMaxSplit);
+  if (nsplit <= 1) return;   // written by the decode itself
+  const size_t row0 = (size_t)su.x * a.Hq + (size_t)(r % a.Hq) * su.y;   // split i is row row0 + i
+  const float2* ml = a.part_ml + row0;
+  const float4* pv = reinterpret_cast<const float4*>(a.part + row0 * D) + (tid & (LPS - 1));
+  // the first passes' partials are requested before the weights are known
+  constexpr int PRE = 4;
+  float4 pre[PRE];
+#pragma unroll
+  for (int k = 0; k < PRE; ++k) pre[k] = pv[(size_t)min(tid / LPS + k * P, nsplit - 1) * LPS];
   float M = -INFINITY;
   for (int i = tid; i < nsplit; i += kWave * W) M = fmaxf(M, ml[i].x);
 #pragma unroll
@@ -333,19 +474,21 @@ __global__ void __launch_bounds__(64 * W) paged_combine_kernel(const float* __re
 #pragma unroll
     for (int k = 0; k < W; ++k) L += sred[1][k];
   }
-  const float4* pv = reinterpret_cast<const float4*>(part + (size_t)r * nsplit * D) + (tid & (LPS - 1));
   float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-  for (int i = tid / LPS; i < nsplit; i += P) {
-    const float4 v = pv[(size_t)i * LPS];
-    const float w = sw[i];
-    if (!(w < 0.f)) {
-      x.x += v.x * w;
-      x.y += v.y * w;
-      x.z += v.z * w;
-      x.w += v.w * w;
-    }
+  auto add = [&](const float4& v, float w) __attribute__((always_inline)) {
+    if (w < 0.f) return;
+    x.x += v.x * w;
+    x.y += v.y * w;
+    x.z += v.z * w;
+    x.w += v.w * w;
+  };
+#pragma unroll
+  for (int k = 0; k < PRE; ++k) {
+    const int i = tid / LPS + k * P;
+    if (i < nsplit) add(pre[k], sw[i]);
   }
+#pragma unroll 4
+  for (int i = tid / LPS + PRE * P; i < nsplit; i += P) add(pv[(size_t)i * LPS], sw[i]);
   sx[tid] = x;
   __syncthreads();
   if (tid >= LPS) return;
@@ -358,8 +501,8 @@ __global__ void __launch_bounds__(64 * W) paged_combine_kernel(const float* __re
     x.w += v.w;
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
-  reinterpret_cast<uint2*>(o + (size_t)r * D)[tid] = pack4_bf16(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
-  if (tid == 0) lse[r] = L > 0.f ? (M + __log2f(L)) * 0.6931471805599453f : -INFINITY;
+  reinterpret_cast<uint2*>(a.o + (size_t)r * D)[tid] = pack4_bf16(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+  if (tid == 0) a.lse[r] = L > 0.f ? (M + __log2f(L)) * 0.6931471805599453f : -INFINITY;
 }
 
 template __global__ void paged_append_kernel<64>(const uint16_t*, const uint16_t*, const int*, const int*, int,
@@ -368,26 +511,29 @@ template __global__ void paged_append_kernel<128>(const uint16_t*, const uint16_
                                                   uint16_t*, uint16_t*, int*, int, int, int);
 template __global__ void paged_decode_kernel<64>(DecodeArgs);
 template __global__ void paged_decode_kernel<128>(DecodeArgs);
-template __global__ void paged_combine_kernel<64, 1>(const float*, const float*, int, uint16_t*, float*);
-template __global__ void paged_combine_kernel<64, 4>(const float*, const float*, int, uint16_t*, float*);
-template __global__ void paged_combine_kernel<128, 1>(const float*, const float*, int, uint16_t*, float*);
-template __global__ void paged_combine_kernel<128, 4>(const float*, const float*, int, uint16_t*, float*);
+template __global__ void paged_combine_kernel<64, 1>(DecodeArgs);
+template __global__ void paged_combine_kernel<64, 4>(DecodeArgs);
+template __global__ void paged_combine_kernel<64, 16>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 1>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 4>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 16>(DecodeArgs);
 
 // ---------------------------------------------------------------- launchers
-// Key splits per (sequence, KV head): enough waves for one round of the
-// resident ones (D = 128: four per CU, D = 64: eight; each sequence's live
-// slots are cut into that many equal ranges on the device), at most one split
-// per four tiles of the table width.
-int paged_nsplit(int S, int Hkv, int max_blocks, int BS, int D) {
-  const long long max_slots = (long long)max_blocks * BS;
-  const long long units = (long long)S * Hkv;
-  long long splits = ((D == 128 ? 4ll : 8ll) * 256 + units - 1) / units;
-  splits = std::min(splits, std::max(1ll, max_slots / (4 * kDecTile)));
-  return (int)std::max(1ll, splits);
+// Units of the decode grid per KV head: one round of the resident waves (D =
+// 128: four per CU, D = 64: eight), and for more sequences than that half a
+// round on top of one unit each, so that long sequences of a ragged batch can
+// still be cut; at most one unit per kMinTiles tiles of the table width.
+int paged_units(int S, int Hkv, int max_blocks, int BS, int D) {
+  const long long round = (D == 128 ? 4ll : 8ll) * 256;
+  const long long slack = (long long)S * Hkv <= (1 << 20) ? (round / 2 + Hkv - 1) / Hkv : 0;
+  const long long tiles = ((long long)max_blocks * BS + kDecTile - 1) / kDecTile;
+  const long long per_seq = (tiles + kMinTiles - 1) / kMinTiles;
+  return (int)std::min(std::max((round + Hkv - 1) / Hkv, S + slack), S * std::max(1ll, per_seq));
 }
-size_t paged_ws_bytes(int S, int Hq, int D, int nsplit) {
-  const size_t rows = (size_t)S * Hq * nsplit;
-  return ((rows * D * sizeof(float) + 255) & ~(size_t)255) + ((rows * 2 * sizeof(float) + 255) & ~(size_t)255);
+static size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
+size_t paged_ws_bytes(int S, int Hq, int D, int units) {
+  const size_t rows = (size_t)units * Hq;
+  return round256(rows * D * sizeof(float)) + round256(rows * sizeof(float2)) + round256((size_t)S * sizeof(int2));
 }
 
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,
@@ -413,17 +559,20 @@ hipError_t launch_paged_evict(const int* slots, int n, int* slot_pos, int num_sl
 
 // One wave a row while it covers the splits in four passes (8 splits at D = 128, 16 at D = 64): many rows
 // then, and one wave without a cross-wave exchange takes 4.9 us for 2,048 rows of two splits.  Beyond that
-// few rows with many splits each: four waves (11.3 -> 4.0 us for 256 rows of 16 splits).
-static void launch_combine(int D, const DecodeArgs& a, uint16_t* o, float* lse, hipStream_t stream) {
+// few rows with many splits each: four waves (11.3 -> 4.0 us for 256 rows of 16 splits), sixteen
+// beyond sixteen passes (9.8 -> 6.2 us for 32 rows of 128).
+static void launch_combine(int D, const DecodeArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)(a.S * a.Hq));
-  const bool wide = a.nsplit > (D == 128 ? 8 : 16);
+  const int pass = D == 128 ? 2 : 4, avg = a.units / a.S;   // splits one wave reads at a time; units per sequence
 #define KVS_COMBINE(DD, WW) \
-  hipLaunchKernelGGL((paged_combine_kernel<DD, WW>), grid, dim3(kWave * WW), 0, stream, a.part, a.part_ml, a.nsplit, o, lse)
+  hipLaunchKernelGGL((paged_combine_kernel<DD, WW>), grid, dim3(kWave * WW), 0, stream, a)
   if (D == 128) {
-    if (wide) KVS_COMBINE(128, 4);
+    if (avg > 16 * pass) KVS_COMBINE(128, 16);
+    else if (avg > 4 * pass) KVS_COMBINE(128, 4);
     else KVS_COMBINE(128, 1);
   } else {
-    if (wide) KVS_COMBINE(64, 4);
+    if (avg > 16 * pass) KVS_COMBINE(64, 16);
+    else if (avg > 4 * pass) KVS_COMBINE(64, 4);
     else KVS_COMBINE(64, 1);
   }
 #undef KVS_COMBINE
@@ -444,19 +593,22 @@ hipError_t launch_paged_decode(const PagedDecode& p) {
   a.max_blocks = p.max_blocks;
   a.BS = p.block_size;
   a.num_blocks = p.num_blocks;
-  a.nsplit = paged_nsplit(p.S, p.Hkv, p.max_blocks, p.block_size, p.D);
+  a.units = paged_units(p.S, p.Hkv, p.max_blocks, p.block_size, p.D);
+  a.o = (uint16_t*)p.o;
+  a.lse = p.lse;
+  const size_t rows = (size_t)a.units * p.Hq;
   a.part = (float*)p.ws;
-  const size_t rows = (size_t)p.S * p.Hq * a.nsplit;
-  a.part_ml = (float*)((char*)p.ws + ((rows * p.D * sizeof(float) + 255) & ~(size_t)255));
+  a.part_ml = (float2*)((char*)p.ws + round256(rows * p.D * sizeof(float)));
+  a.seq_units = (int2*)((char*)a.part_ml + round256(rows * sizeof(float2)));
   a.scale_log2 = p.scale * 1.4426950408889634f;
-  const dim3 grid((unsigned)((long long)p.S * p.Hkv * a.nsplit));
+  const dim3 grid((unsigned)((long long)a.units * p.Hkv));
   prof_begin("paged_decode", p.stream);
   if (p.D == 128) hipLaunchKernelGGL(paged_decode_kernel<128>, grid, dim3(64), 0, p.stream, a);
   else hipLaunchKernelGGL(paged_decode_kernel<64>, grid, dim3(64), 0, p.stream, a);
   prof_end(p.stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  launch_combine(p.D, a, (uint16_t*)p.o, p.lse, p.stream);
+  launch_combine(p.D, a, p.stream);
   return hipGetLastError();
 }
 
