@@ -67,7 +67,7 @@ void head_grouping(kvs::Problem& p) {
 
 size_t fwd_ws(int B, long long ntok) { return kvs::ws_kstats_bytes(B, (int)ntok); }
 size_t bwd_ws(int B, int T, long long ntok, int Hq, int Hkv, int D) {
-  return kvs::ws_kstats_bytes(B, (int)ntok) + kvs::ws_delta_bytes(Hq, (int)ntok) + kvs::ws_split_bytes(B, T, Hkv, D);
+  return kvs::ws_kstats_bytes(B, (int)ntok) + kvs::ws_delta_bytes(Hq, (int)ntok) + kvs::ws_split_bytes(B, T, Hkv, Hq / Hkv, D);
 }
 
 kvs_status_t check_ws(void* ws, size_t have, size_t need) {

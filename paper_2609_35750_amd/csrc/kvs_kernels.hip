@@ -62,8 +62,9 @@ struct ColArgs {
   const int* cu;
   uint16_t* dk;
   uint16_t* dv;
-  const int* plan;      // [B * nkt][2]: chunks of the key block (1 = not split), first slot
-  const int2* items;    // [B * nkt + capE]: (key block, chunk) work items, longest first; (-1, 0) unused
+  const int* plan;      // [B * nkt][2]: parts of the key block (1 = not split), first slot
+  const int2* items;    // [B * nkt + capE]: (key block, part) work items, longest first
+  int* ctl;             // PlanCtl
   float* part;          // [capE * Hkv][2][kColKeys][D] fp32 partial dV, dK of split blocks
   int B, T, Hq, Hkv, G, nkt, ntok;
   int capE;             // slots per KV head (0: no splitting)
@@ -73,9 +74,23 @@ struct ColArgs {
   float scale;
 };
 
-// Row-step chunk of a split key block: 64 row-steps of 64 query rows; blocks
-// whose span exceeds two chunks are split (see split_plan_kernel).
+// Parts of a split key block, in steps of 64 query rows x one q-head (see
+// split_plan_kernel): at least kMinChunk steps, at most kSplitRowSteps row-steps
+// (times G q-heads); kSplitShare parts make up one CU's share of all steps.
 constexpr int kSplitRowSteps = 64;
+constexpr int kMinChunk = 8;
+constexpr int kSplitShare = 3;
+constexpr int kCUs = 256;
+
+// Control words of the column kernel, written by the plan: the number of work
+// items, of split blocks, and the work queues' next items.
+struct PlanCtl {
+  int nitems, nsplit;
+  int next[kCUs];
+};
+// One queue per KV head where the KV heads divide the CUs (workgroup w then
+// keeps to head w % Hkv, and with it an XCD to few heads), else one for all.
+__host__ __device__ __forceinline__ int queue_count(int Hkv) { return kCUs % Hkv == 0 ? Hkv : 1; }
 
 // LSE / Delta layout: fixed [B][Hq][T], varlen [Hq][ntok].
 __device__ __forceinline__ long long lse_index(int varlen, int ntok, int Hq, int T, int b, int h, int tok0, int i) {
@@ -627,29 +642,44 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // (P <= 1; fp16 keeps 3 more mantissa bits than bf16 for dS = P dP)
   __shared__ __attribute__((aligned(1024))) f16x8 sP[2 * 4 * 2 * 2 * kWave];
   __shared__ int sEmax[4];
+  __shared__ int sNext;
 
-  // Work item of this workgroup (longest first, see split_plan_kernel): a
-  // whole key block, or one row chunk of a split block; one KV head each.
-  const int g = blockIdx.x % a.Hkv;
-  const int2 item = a.items[blockIdx.x / a.Hkv];
-  if (item.x < 0) return;   // unused list entry
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool role_dk = wave >= 4;
+  const int kw = wave & 3;
+
+  // Work items (longest first, see split_plan_kernel): a whole key block, or
+  // one part of a split block; one KV head each.  The grid is one workgroup a
+  // CU (it fills the CU); each takes the next item of its queue when it is
+  // done, the first one by its index.  Every item is an iteration, and the
+  // queue's counter only grows, so each workgroup ends after at most all items.
+  // (One workgroup per possible item left those without one to be started and
+  // ended in turn behind the last items, as many as there are unused slots.)
+  PlanCtl* ctl = reinterpret_cast<PlanCtl*>(a.ctl);
+  const int nq = queue_count(a.Hkv), queue = nq > 1 ? blockIdx.x % a.Hkv : 0;
+  const int nidx = nq > 1 ? ctl->nitems : ctl->nitems * a.Hkv;
+  int idx = nq > 1 ? blockIdx.x / a.Hkv : blockIdx.x;
+  const bool more = (int)gridDim.x / nq < nidx;   // items beyond the first ones
+  while (idx < nidx) {
+  const int g = nq > 1 ? queue : idx % a.Hkv;
+  const int2 item = a.items[nq > 1 ? idx : idx / a.Hkv];
   const int b = item.x / a.nkt, kt = item.x % a.nkt, chunk = item.y;
   const int nchunk = a.plan[2 * item.x], slot0 = a.plan[2 * item.x + 1];
   const Trace tr = trace_of(a.cu, b, a.T, a.ntok);
-  const int j0 = kt * kColKeys;
-  if (j0 >= tr.L) return;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool role_dk = wave >= 4;
-  const int kw = wave & 3;
+  const int j0 = kt * kColKeys;   // < tr.L: the plan lists no block past its trace
+  // per-lane constants are recomputed for every item: held across items they cost registers the loop lacks
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
   const int half = lane >> 5, col = lane & 31;
+  const auto rl = Lay<D>::row_lane(lane);
+  const int tl = Lay<D>::tr_lo(lane), th = Lay<D>::tr_hi(lane);
+  RowStager<D, kQStep, 8> qst;
+  qst.init(wave, lane, (long long)a.Hq * D);
   const int j = j0 + 32 * kw + col;
   const bool key_ok = j < tr.L;
   const int jc = min(j, tr.L - 1);
   const int ej = key_ok ? min(a.evict[tr.tok0 + j], tr.L) : 0;
   const unsigned kspan = key_ok ? (unsigned)(ej - j) : 0u;   // rows j .. ej - 1 see this key
-  const auto rl = Lay<D>::row_lane(lane);
-  const int tl = Lay<D>::tr_lo(lane), th = Lay<D>::tr_hi(lane);
   int emin_w = key_ok ? ej : INT_MAX, emax_w = key_ok ? ej : INT_MIN;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -657,8 +687,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     emax_w = max(emax_w, __shfl_xor(emax_w, off));
   }
   if (!role_dk && lane == 0) sEmax[kw] = emax_w;
-  RowStager<D, kQStep, 8> qst;
-  qst.init(wave, lane, (long long)a.Hq * D);
 
   // K (dV waves) or V (dK waves) of this lane's key: the B operand of S or dP
   bf16x8 kvreg[KS];
@@ -670,21 +698,22 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
   __syncthreads();
   const int emax_wg = max(max(sEmax[0], sEmax[1]), max(sEmax[2], sEmax[3]));
-  int qs_lo = j0 / kQStep;
-  int qs_hi = (emax_wg + kQStep - 1) / kQStep;
+  const int qs_lo = j0 / kQStep;
+  const int qs_hi = (emax_wg + kQStep - 1) / kQStep;
+  int steps = max(qs_hi - qs_lo, 0) * a.G, step0 = 0;   // this item: steps step0 .. step0 + steps - 1 of the block's
   if (nchunk > 1) {
-    qs_lo += chunk * kSplitRowSteps;
-    qs_hi = min(qs_hi, qs_lo + kSplitRowSteps);
+    const int per = (steps + nchunk - 1) / nchunk;
+    step0 = min(chunk * per, steps);
+    steps = min(per, steps - step0);
   }
-  const int steps = max(qs_hi - qs_lo, 0) * a.G;
 
   f32x16 acc[DB];   // dV^T (dV waves) or dK^T (dK waves): rows d, column = this lane's key
 #pragma unroll
   for (int d = 0; d < DB; ++d) acc[d] = f32x16{};
 
   auto stage = [&](uint16_t* q_, uint16_t* o_, float* l_, float* d_, int step) __attribute__((always_inline)) {
-    const int i0 = (qs_lo + step / a.G) * kQStep;
-    const int h = g * a.G + step % a.G;
+    const int i0 = (qs_lo + (step0 + step) / a.G) * kQStep;
+    const int h = g * a.G + (step0 + step) % a.G;
     const long long base = ((long long)tr.tok0 * a.Hq + h) * D;
     qst.issue(lds_addr(q_), a.q + base, (long long)a.Hq * D, i0, tr.L - 1, wave);
     qst.issue(lds_addr(o_), a.dout + base, (long long)a.Hq * D, i0, tr.L - 1, wave);
@@ -887,7 +916,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int d = 0; d < DB; ++d) acc[d] = mfma32(tB[t][d], sb[1][t], acc[d]);
   };
   auto dv_step = [&](int step, const uint16_t* cQ, const uint16_t* cO, const float* cL) __attribute__((always_inline)) {
-    const int i0 = (qs_lo + step / a.G) * kQStep;
+    const int i0 = (qs_lo + (step0 + step) / a.G) * kQStep;
     const int c0 = adjust_class(tile_class(i0, i0 + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     const int c1 = adjust_class(tile_class(i0 + 32, i0 + 64, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     if (c0 == kFull && c1 == kFull) {
@@ -912,7 +941,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   };
   auto dk_step = [&](int step, const uint16_t* cQ, const uint16_t* cO, const float* cD) __attribute__((always_inline)) {
-    const int i0 = (qs_lo + step / a.G) * kQStep;
+    const int i0 = (qs_lo + (step0 + step) / a.G) * kQStep;
     const int c0 = adjust_class(tile_class(i0, i0 + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     const int c1 = adjust_class(tile_class(i0 + 32, i0 + 64, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     if (c0 != kEmpty && c1 != kEmpty) {
@@ -962,6 +991,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (role_dk) run(std::true_type{});
   else run(std::false_type{});
 
+  if (threadIdx.x == 0) sNext = more ? atomicAdd(&ctl->next[queue], 1) : nidx;
   if (nchunk > 1) {
     // fp32 partial sums of this chunk: [slot][dV, dK][key in block][d]
     float* dst = a.part + (((size_t)(slot0 + chunk) * a.Hkv + g) * 2 + (role_dk ? 1 : 0)) * kColKeys * D +
@@ -983,32 +1013,46 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         *reinterpret_cast<uint2*>(dst + 32 * d + 8 * q4 + 4 * half) =
             pack4_bf16(acc[d][4 * q4] * sc, acc[d][4 * q4 + 1] * sc, acc[d][4 * q4 + 2] * sc, acc[d][4 * q4 + 3] * sc);
   }
+  __syncthreads();   // sNext; and every wave is done with the LDS of this item
+  idx = __builtin_amdgcn_readfirstlane(sNext);
+  }
 }
 
 // ---------------------------------------------------------------- work plan of the column kernel
 // A key block whose keys stay visible for many query rows (the prompt,
 // long-lived summaries) would be one long workgroup and set the kernel's
-// critical path.  Blocks spanning more than 2 * kSplitRowSteps row-steps are
-// cut into chunks of kSplitRowSteps row-steps; every chunk gets a slot of fp32
-// partial sums, and the chunks are added in slot order afterwards
+// critical path.  A dK/dV workgroup fills a CU, so a CU's share of the work is
+// total steps x Hkv / kCUs.  Blocks longer than that share are cut into equal
+// parts of at most 1 / kSplitShare of it; shorter ones start early enough whole.
+// Parts stay within [kMinChunk, kSplitRowSteps * G] steps (below, a workgroup's
+// start and end outweigh its steps; above, long traces would be left with a
+// long last item) and blocks of up to two of the bound are not cut.  Every part
+// gets a slot of fp32 partial sums, and the parts are added in order afterwards
 // (deterministic).  Slots are granted in key-block order while capE lasts;
-// later blocks stay whole.  All work items (whole blocks and chunks) are then
-// listed longest first (counting sort on the row-step count), so the longest
-// items start first.  One workgroup of 1024 threads; block spans come from the
-// 64-key tile statistics.
+// later blocks stay whole.  All work items (whole blocks and parts) are then
+// listed longest first (counting sort on the step count).  One workgroup of
+// 1024 threads; block spans come from the 64-key tile statistics.
+// dK/dV time with parts of 64 row-steps only, cut beyond 128, and with these:
+// 24 traces of 100 to 1,500 tokens (16/2 heads, D = 128) 336 -> 141 us, two of
+// 4,097 (32/8) 450 -> 338 us, one of 8,191 (24/8, D = 64) 468 -> 198 us.  Parts
+// of 1/2 and 1/4 share and a threshold of 2/3 or 4/5 share: within 5% of that.
 __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict__ kstats, const int* __restrict__ cu,
-                                                          int B, int T, int ntok, int nkt, int capE,
-                                                          int* __restrict__ plan, int2* __restrict__ items) {
-  constexpr int NBK = 2048;   // sort buckets: row-step counts 0 .. 2047 (longer ones share the last bucket)
-  __shared__ int scan[1024];
+                                                          int B, int T, int ntok, int nkt, int G, int Hkv, int capE,
+                                                          int grid, int* __restrict__ plan, int2* __restrict__ items,
+                                                          int* __restrict__ split, PlanCtl* __restrict__ ctl) {
+  constexpr int NBK = 2048, NW = 1024 / kWave;   // sort buckets, waves
   __shared__ int bucket[NBK];
-  const int tid = threadIdx.x;
-  const int nblocks = B * nkt, nitems = nblocks + capE;
-  for (int i = tid; i < NBK; i += 1024) bucket[i] = 0;
-  for (int e = tid; e < nitems; e += 1024) items[e] = make_int2(-1, 0);
+  __shared__ int wsum[4][NW];
+  __shared__ int nsplit_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nblocks = B * nkt;
+  bucket[tid] = bucket[tid + 1024] = 0;
+  if (tid == 0) nsplit_s = 0;
+  if (tid < kCUs) ctl->next[tid] = grid / queue_count(Hkv);   // the first items are taken by index
   const int per = (nblocks + 1023) / 1024;
   const int b0 = min(tid * per, nblocks), b1 = min(b0 + per, nblocks);
-  auto span_of = [&](int blk) {   // query row-steps [j0/64, ceil(emax/64)) of the block; 0 past the trace
+  // row-steps of a block: [j0/64, ceil(emax/64)); 0 past the trace
+  auto read_rows = [&](int blk) {
     const int b = blk / nkt, kt = blk % nkt;
     const Trace tr = trace_of(cu, b, T, ntok);
     const int j0 = kt * kColKeys;
@@ -1016,111 +1060,146 @@ __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict
     const int t0 = j0 / kKeyTile, nt = (tr.L + kKeyTile - 1) / kKeyTile;
     int emax = kstats[kstat_index(b, tr.tok0, t0, kKeyTile)].y;
     if (t0 + 1 < nt) emax = max(emax, kstats[kstat_index(b, tr.tok0, t0 + 1, kKeyTile)].y);
-    return (emax + kQStep - 1) / kQStep - j0 / kQStep;
+    return max((emax + kQStep - 1) / kQStep - j0 / kQStep, 1);
   };
-  auto chunks_of = [](int span) {
-    return span > 2 * kSplitRowSteps ? (span + kSplitRowSteps - 1) / kSplitRowSteps : 0;
-  };
-  // Sort key (larger first).  One trace (or more than NBK / 8): the row-step
-  // count.  Otherwise the row-step count in classes of Q >= 8 steps, then the
-  // trace, so that items of one trace with about the same length are listed
-  // together and run side by side (they share Q / dO rows in an XCD's L2);
-  // the longest class still starts first, so the tail grows by less than Q
-  // steps.  Keys stay below NBK: nclass * B <= NBK.
-  const bool by_trace = B > 1 && B <= NBK / 8;
-  const int Q = by_trace ? max(8, (NBK + NBK / B - 1) / (NBK / B)) : 1;
-  const int nclass = (NBK + Q - 1) / Q;
-  auto key_of = [&](int rows, int blk) {
-    const int r = min(rows, NBK - 1);
-    return by_trace ? min(r / Q, nclass - 1) * B + blk / nkt : r;
-  };
-  int tot = 0;
-  for (int blk = b0; blk < b1; ++blk) tot += chunks_of(span_of(blk));
-  scan[tid] = tot;
+  // at most one block a thread: its steps and parts stay in registers
+  const int own = per == 1 && b0 < b1 ? read_rows(b0) * G : 0;
+  int own_parts = 1;
+  auto steps_of = [&](int blk) { return per == 1 ? own : read_rows(blk) * G; };
+  int sum = 0, steps_sum = 0;   // row-steps: at most 2^14 a block, 2^13 blocks of the longest traces
+  for (int blk = b0; blk < b1; ++blk) sum += steps_of(blk) / G;
+  steps_sum = wave_last(wave_scan(sum));
+  if (lane == 0) wsum[0][wave] = steps_sum;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = tid >= off ? scan[tid - off] : 0;
-    __syncthreads();
-    scan[tid] += v;
-    __syncthreads();
-  }
-  int run = scan[tid] - tot;   // exclusive prefix of requested slots
+  long long total = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) total += wsum[0][w];
+  const long long share = total * G * Hkv / kCUs;   // steps of one CU
+  const long long most = max((long long)kSplitRowSteps * G, (long long)kMinChunk);
+  const int chunk = (int)min(max(share / kSplitShare, (long long)kMinChunk), most);
+  const int whole = (int)min(max(share, 2ll * kMinChunk), 2 * most);
+  auto parts_of = [&](int steps) { return steps > whole ? (steps + chunk - 1) / chunk : 0; };
+  int tot = 0, top = 1;   // requested slots; longest item
   for (int blk = b0; blk < b1; ++blk) {
-    const int span = span_of(blk), w = chunks_of(span);
+    const int steps = steps_of(blk), w = parts_of(steps);
+    tot += w;
+    top = max(top, w > 0 ? (steps + w - 1) / w : steps);
+  }
+  int incl = wave_scan(tot);
+  top = wave_max(top);
+  if (lane == kWave - 1) wsum[1][wave] = incl;
+  if (lane == 0) wsum[2][wave] = top;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) incl += wsum[1][w];
+    top = max(top, wsum[2][w]);
+  }
+  int run = incl - tot;   // exclusive prefix of requested slots
+  // Sort key (larger first): the step count in equal classes (blocks left
+  // whole for want of slots may exceed the last one).  One trace (or more than
+  // NBK / 8): NBK classes.  Otherwise the class, then the trace, so that items
+  // of one trace with about the same length are listed together and run side
+  // by side (they share Q / dO rows in an XCD's L2); the classes are then at
+  // least 8 row-steps wide, or a quarter of a chunk if that is less; the
+  // longest class still starts first, so the tail grows by less than a class.
+  // Keys stay below NBK: nclass * B <= NBK.
+  const bool by_trace = B > 1 && B <= NBK / 8;
+  const int nclass = by_trace ? NBK / B : NBK;
+  const int width = max((top + nclass) / nclass, by_trace ? min(8 * G, max(chunk / 4, 1)) : 1);
+  auto key_of = [&](int steps, int blk) {
+    const int c = min(steps / width, nclass - 1);
+    return by_trace ? c * B + blk / nkt : c;
+  };
+  for (int blk = b0; blk < b1; ++blk) {
+    const int steps = steps_of(blk), w = parts_of(steps);
     const bool grant = w > 0 && run + w <= capE;
-    plan[2 * blk] = grant ? w : 1;
+    own_parts = grant ? w : 1;
+    plan[2 * blk] = own_parts;
     plan[2 * blk + 1] = grant ? run : 0;
+    if (grant) split[atomicAdd(&nsplit_s, 1)] = blk;
     run += w;
-    if (span == 0) continue;
-    if (grant)
-      for (int c = 0; c < w; ++c) atomicAdd(&bucket[key_of(min(kSplitRowSteps, span - c * kSplitRowSteps), blk)], 1);
-    else
-      atomicAdd(&bucket[key_of(span, blk)], 1);
+    if (steps == 0) continue;
+    const int len = (steps + own_parts - 1) / own_parts;
+    for (int c = 0; c < own_parts; ++c) atomicAdd(&bucket[key_of(max(min(len, steps - c * len), 0), blk)], 1);
   }
   __syncthreads();
   // bucket start positions, longest first: thread t owns buckets NBK-1-2t and NBK-2-2t
   const int khi = NBK - 1 - 2 * tid, klo = khi - 1;
   const int chi = bucket[khi], clo = bucket[klo];
-  scan[tid] = chi + clo;
+  incl = wave_scan(chi + clo);
+  if (lane == kWave - 1) wsum[3][wave] = incl;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = tid >= off ? scan[tid - off] : 0;
-    __syncthreads();
-    scan[tid] += v;
-    __syncthreads();
+  int all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) incl += wsum[3][w];
+    all += wsum[3][w];
   }
-  const int excl = scan[tid] - chi - clo;
-  bucket[khi] = excl;
-  bucket[klo] = excl + chi;
+  bucket[khi] = incl - chi - clo;
+  bucket[klo] = incl - clo;
+  if (tid == 0) {
+    ctl->nitems = all;
+    ctl->nsplit = nsplit_s;
+  }
   __syncthreads();
   for (int blk = b0; blk < b1; ++blk) {
-    const int span = span_of(blk);
-    if (span == 0) continue;
-    const int nc = plan[2 * blk];
-    if (nc > 1) {
-      for (int c = 0; c < nc; ++c)
-        items[atomicAdd(&bucket[key_of(min(kSplitRowSteps, span - c * kSplitRowSteps), blk)], 1)] = make_int2(blk, c);
-    } else {
-      items[atomicAdd(&bucket[key_of(span, blk)], 1)] = make_int2(blk, 0);
-    }
+    const int steps = steps_of(blk), nc = per == 1 ? own_parts : plan[2 * blk];
+    if (steps == 0) continue;
+    const int len = (steps + nc - 1) / nc;
+    for (int c = 0; c < nc; ++c)
+      items[atomicAdd(&bucket[key_of(max(min(len, steps - c * len), 0), blk)], 1)] = make_int2(blk, c);
   }
 }
 
-// Sum of the chunk partials of split key blocks, in chunk order; dK scaled.
-// kReduceSplit workgroups per (key block, KV head), each summing a slice of
-// the block's keys; blocks that were not split exit.
-constexpr int kReduceSplit = 8;
+// Sum of the parts' partials of split key blocks, in part order; dK scaled.
+// The split blocks are listed by the plan, and a fixed grid walks the float4
+// slices of 256 threads of all of them (dV and dK): bound by reading the
+// partials, so every thread keeps several parts' loads in flight.
+constexpr int kReduceGrid = 2048;
 template <int D>
-__global__ void __launch_bounds__(256) split_reduce_kernel(const int* __restrict__ plan, const float* __restrict__ part,
-                                                           const int* __restrict__ cu, uint16_t* __restrict__ dk,
-                                                           uint16_t* __restrict__ dv, int B, int T, int ntok,
-                                                           int nkt, int Hkv, float scale) {
-  const int sub = blockIdx.x % kReduceSplit, wg = blockIdx.x / kReduceSplit;
-  const int g = wg % Hkv, blk = wg / Hkv;
-  const int nc = plan[2 * blk], s0 = plan[2 * blk + 1];
-  if (nc <= 1) return;
-  const int b = blk / nkt, kt = blk % nkt;
-  const Trace tr = trace_of(cu, b, T, ntok);
-  constexpr int PER = kColKeys * D / kReduceSplit / 256;   // elements per thread
-  static_assert(PER % 4 == 0 && PER >= 4, "reduce slice must be whole float4s per thread");
-  for (int which = 0; which < 2; ++which) {
-    for (int q = 0; q < PER / 4; ++q) {
-      const int e = sub * (kColKeys * D / kReduceSplit) + (q * 256 + threadIdx.x) * 4;   // element of [key][d]
-      const int key = e / D, d = e % D;
-      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int c = 0; c < nc; ++c) {
-        const float4 v = *reinterpret_cast<const float4*>(part + (((size_t)(s0 + c) * Hkv + g) * 2 + which) * kColKeys * D + e);
-        sum.x += v.x;
-        sum.y += v.y;
-        sum.z += v.z;
-        sum.w += v.w;
+__global__ void __launch_bounds__(256) split_reduce_kernel(const PlanCtl* __restrict__ ctl,
+                                                           const int* __restrict__ plan, const int* __restrict__ split,
+                                                           const float* __restrict__ part, const int* __restrict__ cu,
+                                                           uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int B,
+                                                           int T, int ntok, int nkt, int Hkv, float scale) {
+  constexpr int kSlices = 2 * kColKeys * D / 4 / 256;   // slices of one block and KV head; the first half is dV
+  constexpr size_t kSlot = (size_t)2 * kColKeys * D;    // floats of one slot
+  const int tasks = ctl->nsplit * Hkv * kSlices;
+  for (int t = blockIdx.x; t < tasks; t += gridDim.x) {
+    const int slice = t % kSlices, bg = t / kSlices, g = bg % Hkv, blk = split[bg / Hkv];
+    const int nc = plan[2 * blk], s0 = plan[2 * blk + 1];
+    const int b = blk / nkt, kt = blk % nkt;
+    const int e = (slice * 256 + threadIdx.x) * 4;   // element of [dV, dK][key][d]
+    const float* src = part + ((size_t)s0 * Hkv + g) * kSlot + e;
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    int c = 0;
+    for (; c + 4 <= nc; c += 4) {
+      float4 v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(src + (size_t)(c + k) * Hkv * kSlot);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        sum.x += v[k].x;
+        sum.y += v[k].y;
+        sum.z += v[k].z;
+        sum.w += v[k].w;
       }
-      const int j = kt * kColKeys + key;
-      if (j < tr.L) {
-        const float sc = which ? scale : 1.f;
-        uint16_t* dst = (which ? dk : dv) + ((size_t)(tr.tok0 + j) * Hkv + g) * D + d;
-        *reinterpret_cast<uint2*>(dst) = pack4_bf16(sum.x * sc, sum.y * sc, sum.z * sc, sum.w * sc);
-      }
+    }
+    for (; c < nc; ++c) {
+      const float4 v = *reinterpret_cast<const float4*>(src + (size_t)c * Hkv * kSlot);
+      sum.x += v.x;
+      sum.y += v.y;
+      sum.z += v.z;
+      sum.w += v.w;
+    }
+    const int which = e / (kColKeys * D), key = e / D % kColKeys, d = e % D;
+    const Trace tr = trace_of(cu, b, T, ntok);
+    const int j = kt * kColKeys + key;
+    if (j < tr.L) {
+      const float sc = which ? scale : 1.f;
+      uint16_t* dst = (which ? dk : dv) + ((size_t)(tr.tok0 + j) * Hkv + g) * D + d;
+      *reinterpret_cast<uint2*>(dst) = pack4_bf16(sum.x * sc, sum.y * sc, sum.z * sc, sum.w * sc);
     }
   }
 }
@@ -1132,10 +1211,10 @@ template __global__ void dq_kernel<64>(RowArgs);
 template __global__ void dq_kernel<128>(RowArgs);
 template __global__ void dkdv_kernel<64>(ColArgs);
 template __global__ void dkdv_kernel<128>(ColArgs);
-template __global__ void split_reduce_kernel<64>(const int*, const float*, const int*, uint16_t*, uint16_t*, int, int,
-                                                 int, int, int, float);
-template __global__ void split_reduce_kernel<128>(const int*, const float*, const int*, uint16_t*, uint16_t*, int, int,
-                                                  int, int, int, float);
+template __global__ void split_reduce_kernel<64>(const PlanCtl*, const int*, const int*, const float*, const int*, uint16_t*, uint16_t*,
+                                                  int, int, int, int, int, float);
+template __global__ void split_reduce_kernel<128>(const PlanCtl*, const int*, const int*, const float*, const int*, uint16_t*, uint16_t*,
+                                                  int, int, int, int, int, float);
 
 // ---------------------------------------------------------------- library-owned scratch (allocation-free forward)
 // Per-key-tile statistics of kvs_evict_attn_fwd_noalloc.  In host code the
@@ -1176,21 +1255,23 @@ static size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // Work plan of the column kernel: plan [B * nkt][2] int, work items
 // [B * nkt + capE] int2, partial sums [capE * Hkv][2][kColKeys][D] fp32.
-// capE: chunk slots per KV head, at most 2048 slots over all KV heads, none
-// when no block can span more than two chunks.
-int split_cap(int B, int T, int Hkv) {
-  const int max_span = (T + kQStep - 1) / kQStep;
-  if (max_span <= 2 * kSplitRowSteps) return 0;
+// capE: slots of parts per KV head, at most 2048 over all KV heads.  Up to
+// 2 * kSplitRowSteps row-steps only the CUs' shares ask for parts: kSplitShare
+// kCUs of them if every block is cut, and one more for each of at most kCUs cut
+// blocks.  None when no block can span more than two least parts.
+int split_cap(int B, int T, int Hkv, int G) {
+  const long long max_span = (T + kQStep - 1) / kQStep, max_steps = max_span * G;
+  if (max_steps <= 2 * kMinChunk) return 0;
   const long long nkt = (T + kColKeys - 1) / kColKeys;
-  const long long per_block = (max_span + kSplitRowSteps - 1) / kSplitRowSteps;
-  const long long cap = std::min<long long>(2048 / Hkv, (long long)B * nkt * per_block);
-  return (int)std::max<long long>(cap, 0);
+  const long long slots = max_span <= 2 * kSplitRowSteps ? std::min(2048, (kSplitShare + 1) * kCUs) : 2048;
+  const long long per_block = (max_steps + kMinChunk - 1) / kMinChunk;
+  return (int)std::min<long long>(slots / Hkv, (long long)B * nkt * per_block);
 }
-size_t ws_split_bytes(int B, int T, int Hkv, int D) {
-  const int capE = split_cap(B, T, Hkv);
+size_t ws_split_bytes(int B, int T, int Hkv, int G, int D) {
+  const int capE = split_cap(B, T, Hkv, G);
   const long long nkt = (T + kColKeys - 1) / kColKeys;
   return round256((size_t)B * nkt * 2 * sizeof(int)) + round256(((size_t)B * nkt + capE) * sizeof(int2)) +
-         round256((size_t)capE * Hkv * 2 * kColKeys * D * sizeof(float));
+         round256(sizeof(PlanCtl)) + round256((size_t)capE * sizeof(int)) + round256((size_t)capE * Hkv * 2 * kColKeys * D * sizeof(float));
 }
 static size_t half_delta_bytes(int Hq, int ntok) { return ws_delta_bytes(Hq, ntok) / 2; }
 
@@ -1281,34 +1362,39 @@ hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* de
   a.flags = p.flags;
   a.scale = p.scale;
   a.scale_log2 = p.scale * 1.4426950408889634f;
-  a.capE = split_cap(p.B, p.T, p.Hkv);
+  a.capE = split_cap(p.B, p.T, p.Hkv, p.G);
+  int* split;   // split blocks
+  // one workgroup a CU, fewer if there cannot be as many items
+  const int grid = (int)std::min<long long>(kCUs, ((long long)a.nkt * p.B + a.capE) * p.Hkv);
   {
     char* w = (char*)split_ws;
     int* plan = (int*)w;
     w += round256((size_t)p.B * a.nkt * 2 * sizeof(int));
     int2* items = (int2*)w;
     w += round256(((size_t)p.B * a.nkt + a.capE) * sizeof(int2));
+    a.ctl = (int*)w;
+    w += round256(sizeof(PlanCtl));
+    split = (int*)w;
+    w += round256((size_t)a.capE * sizeof(int));
     a.plan = plan;
     a.items = items;
     a.part = (float*)w;
     hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, p.stream, kstats, p.cu, p.B, p.T, p.ntok, a.nkt,
-                       a.capE, plan, items);
+                       p.G, p.Hkv, a.capE, grid, plan, items, split, (PlanCtl*)a.ctl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const long long nblk = ((long long)a.nkt * p.B + a.capE) * p.Hkv;
   prof_begin("bwd_dkdv", p.stream);
-  if (p.D == 128) hipLaunchKernelGGL(dkdv_kernel<128>, dim3((unsigned)nblk), dim3(512), 0, p.stream, a);
-  else hipLaunchKernelGGL(dkdv_kernel<64>, dim3((unsigned)nblk), dim3(512), 0, p.stream, a);
+  if (p.D == 128) hipLaunchKernelGGL(dkdv_kernel<128>, dim3(grid), dim3(512), 0, p.stream, a);
+  else hipLaunchKernelGGL(dkdv_kernel<64>, dim3(grid), dim3(512), 0, p.stream, a);
   prof_end(p.stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.capE == 0) return e;
-  const dim3 rgrid((unsigned)((long long)p.B * a.nkt * p.Hkv * kReduceSplit));
   if (p.D == 128)
-    hipLaunchKernelGGL(split_reduce_kernel<128>, rgrid, dim3(256), 0, p.stream, a.plan, a.part, p.cu,
+    hipLaunchKernelGGL(split_reduce_kernel<128>, dim3(kReduceGrid), dim3(256), 0, p.stream, (const PlanCtl*)a.ctl, a.plan, split, a.part, p.cu,
                        (uint16_t*)p.dk, (uint16_t*)p.dv, p.B, p.T, p.ntok, a.nkt, p.Hkv, p.scale);
   else
-    hipLaunchKernelGGL(split_reduce_kernel<64>, rgrid, dim3(256), 0, p.stream, a.plan, a.part, p.cu,
+    hipLaunchKernelGGL(split_reduce_kernel<64>, dim3(kReduceGrid), dim3(256), 0, p.stream, (const PlanCtl*)a.ctl, a.plan, split, a.part, p.cu,
                        (uint16_t*)p.dk, (uint16_t*)p.dv, p.B, p.T, p.ntok, a.nkt, p.Hkv, p.scale);
   return hipGetLastError();
 }

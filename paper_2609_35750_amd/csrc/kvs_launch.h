@@ -42,7 +42,7 @@ constexpr size_t kNoAllocScratchBytes = 256 * 1024;
 constexpr int kMaxDevices = 64;
 hipError_t noalloc_scratch(void** ptr);
 size_t ws_delta_bytes(int Hq, int ntok);
-size_t ws_split_bytes(int B, int T, int Hkv, int D);
+size_t ws_split_bytes(int B, int T, int Hkv, int G, int D);
 
 // Launchers.  Each returns the hipError_t of its launch(es).
 hipError_t launch_kstats(const Problem& p, int BN, int2* kstats);

@@ -142,18 +142,6 @@ struct DecodeUnit {
   int s, nslots, first, n, chunk;   // sequence, its slots, its first unit, its units, this one among them
 };
 
-// Inclusive prefix sum over the 64 lanes (data-parallel moves: no LDS round trips).
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // last lane of rows 0, 2 to rows 1, 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2, 3
-  return x;
-}
-__device__ __forceinline__ int wave_last(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
-
 constexpr int kTileCap = 1 << 22;   // tiles of one sequence the plan tells apart (134 M slots); exact in fp32
 // x / y for x >= 0, y >= 1: float quotient, corrected, where x is exact in fp32 (an integer division of the
 // compiler's is several times the dependent instructions, on every wave's way to its first load)
