@@ -329,8 +329,10 @@ struct RowStager {
   // lds: LDS byte address of the tile (lds_addr).
   __device__ __forceinline__ void issue(uint32_t lds, const uint16_t* __restrict__ g, long long row_stride, int row0,
                                         int rmax, int wave) const {
-    const uint16_t* base = uniform_ptr(g + (long long)row0 * row_stride);
-    const uint32_t lim = limit(rmax - row0, row_stride);
+    issue_at(lds, uniform_ptr(g + (long long)row0 * row_stride), limit(rmax - row0, row_stride), wave);
+  }
+  // the same from the address of the tile's first row (wave-uniform) and its limit()
+  __device__ __forceinline__ void issue_at(uint32_t lds, const void* base, uint32_t lim, int wave) const {
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
       const int n = wave + i * NW;
@@ -343,6 +345,10 @@ struct RowStager {
 __device__ __forceinline__ void stage_words(uint32_t lds, const void* __restrict__ g, int i0, int imax, int lane) {
   const char* base = uniform_ptr((const char*)g + 4ll * i0);
   dma_b32(base, 4u * (uint32_t)(min(i0 + lane, imax) - i0), lds);
+}
+// the same from the address of the first value (wave-uniform), dmax more values being valid
+__device__ __forceinline__ void stage_words_at(uint32_t lds, const void* base, int dmax, int lane) {
+  dma_b32(base, 4u * (uint32_t)min(lane, dmax), lds);
 }
 
 // Wait for this wave's outstanding global loads (including LDS-direct ones).

@@ -711,15 +711,38 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
   for (int d = 0; d < DB; ++d) acc[d] = f32x16{};
 
-  auto stage = [&](uint16_t* q_, uint16_t* o_, float* l_, float* d_, int step) __attribute__((always_inline)) {
-    const int i0 = (qs_lo + (step0 + step) / a.G) * kQStep;
-    const int h = g * a.G + (step0 + step) % a.G;
-    const long long base = ((long long)tr.tok0 * a.Hq + h) * D;
-    qst.issue(lds_addr(q_), a.q + base, (long long)a.Hq * D, i0, tr.L - 1, wave);
-    qst.issue(lds_addr(o_), a.dout + base, (long long)a.Hq * D, i0, tr.L - 1, wave);
-    const long long lb = lse_index(a.varlen, a.ntok, a.Hq, a.T, b, h, tr.tok0, 0);
-    if (wave == 6) stage_words(lds_addr(l_), a.lse + lb, i0, tr.L - 1, lane);   // LSE * log2(e)
-    if (wave == 7) stage_words(lds_addr(d_), a.delta + lb, i0, tr.L - 1, lane);
+  // First row of a step and the byte offsets of its first Q / dO row and its
+  // first LSE / Delta value, advanced step by step: from the step number they
+  // are a division by G and some forty scalar instructions of every wave,
+  // ahead of the step's copies.
+  struct Pos {
+    int i0, hh;   // first row, q-head of the group
+  };
+  struct Src {
+    Pos at;
+    long long row, word;
+  };
+  const long long row_step = 2ll * D, row_wrap = 2ll * D * ((long long)kQStep * a.Hq - a.G);
+  const long long word_step = 4ll * (a.varlen ? a.ntok : a.T), word_wrap = 4ll * kQStep - a.G * word_step;
+  auto advance = [&](Pos& p) __attribute__((always_inline)) {
+    const bool wrap = ++p.hh == a.G;
+    p.hh = wrap ? 0 : p.hh;
+    p.i0 += wrap ? kQStep : 0;
+    return wrap;
+  };
+  const Pos first = {(qs_lo + step0 / a.G) * kQStep, step0 % a.G};
+  const Src src0 = {first, row_step * ((long long)(tr.tok0 + first.i0) * a.Hq + g * a.G + first.hh),
+                    4ll * lse_index(a.varlen, a.ntok, a.Hq, a.T, b, g * a.G + first.hh, tr.tok0, first.i0)};
+  auto stage = [&](uint16_t* q_, uint16_t* o_, float* l_, float* d_, Src& s) __attribute__((always_inline)) {
+    const int dr = tr.L - 1 - s.at.i0;
+    const uint32_t lim = qst.limit(dr, (long long)a.Hq * D);
+    qst.issue_at(lds_addr(q_), (const char*)a.q + s.row, lim, wave);
+    qst.issue_at(lds_addr(o_), (const char*)a.dout + s.row, lim, wave);
+    if (wave == 6) stage_words_at(lds_addr(l_), (const char*)a.lse + s.word, dr, lane);   // LSE * log2(e)
+    if (wave == 7) stage_words_at(lds_addr(d_), (const char*)a.delta + s.word, dr, lane);
+    const bool wrap = advance(s.at);
+    s.row += row_step + (wrap ? row_wrap : 0);
+    s.word += word_step + (wrap ? word_wrap : 0);
   };
   const int jw0 = j0 + 32 * kw;
   auto xslot = [&](int step, int blk, int t) __attribute__((always_inline)) { return sP + ((((step & 1) * 4 + kw) * 2 + blk) * 2 + t) * kWave + lane; };
@@ -915,8 +938,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int d = 0; d < DB; ++d) acc[d] = mfma32(tB[t][d], sb[1][t], acc[d]);
   };
-  auto dv_step = [&](int step, const uint16_t* cQ, const uint16_t* cO, const float* cL) __attribute__((always_inline)) {
-    const int i0 = (qs_lo + (step0 + step) / a.G) * kQStep;
+  auto dv_step = [&](int step, int i0, const uint16_t* cQ, const uint16_t* cO, const float* cL) __attribute__((always_inline)) {
     const int c0 = adjust_class(tile_class(i0, i0 + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     const int c1 = adjust_class(tile_class(i0 + 32, i0 + 64, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     if (c0 == kFull && c1 == kFull) {
@@ -940,8 +962,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
   };
-  auto dk_step = [&](int step, const uint16_t* cQ, const uint16_t* cO, const float* cD) __attribute__((always_inline)) {
-    const int i0 = (qs_lo + (step0 + step) / a.G) * kQStep;
+  auto dk_step = [&](int step, int i0, const uint16_t* cQ, const uint16_t* cO, const float* cD) __attribute__((always_inline)) {
     const int c0 = adjust_class(tile_class(i0, i0 + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     const int c1 = adjust_class(tile_class(i0 + 32, i0 + 64, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
     if (c0 != kEmpty && c1 != kEmpty) {
@@ -965,20 +986,26 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   auto run = [&](auto dk_tag) __attribute__((always_inline)) {
     constexpr bool DK = decltype(dk_tag)::value;
     int step = 0;
+    Src next = src0;   // the tile staged next
+    Pos cur = first;   // the tile this wave computes next
     auto body = [&](const uint16_t* cQ, const uint16_t* cO, const float* cD, const uint16_t* nQ, const uint16_t* nO,
                     const float* nL, uint16_t* zQ, uint16_t* zO, float* zL, float* zD) __attribute__((always_inline)) {
-      if (step + 2 < steps) stage(zQ, zO, zL, zD, step + 2);
-      if (DK) dk_step(step, cQ, cO, cD);
-      else if (step + 1 < steps) dv_step(step + 1, nQ, nO, nL);
+      if (step + 2 < steps) stage(zQ, zO, zL, zD, next);
+      if (DK) dk_step(step, cur.i0, cQ, cO, cD);
+      else if (step + 1 < steps) dv_step(step + 1, cur.i0, nQ, nO, nL);
+      advance(cur);
       wait_vm();   // tile step + 2 has landed (the dV waves read it next step)
       __syncthreads();
       ++step;
     };
-    if (steps > 0) stage(sQ0, sO0, sL0, sD0, 0);
-    if (steps > 1) stage(sQ1, sO1, sL1, sD1, 1);
+    if (steps > 0) stage(sQ0, sO0, sL0, sD0, next);
+    if (steps > 1) stage(sQ1, sO1, sL1, sD1, next);
     wait_vm();
     __syncthreads();
-    if (!DK && steps > 0) dv_step(0, sQ0, sO0, sL0);
+    if (!DK && steps > 0) {
+      dv_step(0, cur.i0, sQ0, sO0, sL0);
+      advance(cur);
+    }
     __syncthreads();
     while (step < steps) {
       body(sQ0, sO0, sD0, sQ1, sO1, sL1, sQ2, sO2, sL2, sD2);
