@@ -327,15 +327,21 @@ fwd_kernel(RowArgs a) {
   const int tl = Lay<D, true>::tr_lo(lane), th = Lay<D, true>::tr_hi(lane);
   FwdStager<D> kvst;
   kvst.init(wave, lane, (long long)a.Hkv * D);
-  // asynchronous staging of sub-tile (kt, sub) of KV head g
-  auto stage = [&](uint16_t* sK, uint16_t* sV, int* sE, int kt, int sub) __attribute__((always_inline)) {
-    const int j0 = kt * kKeyTile + sub * BN;
-    const long long base = ((long long)rt.tr.tok0 * a.Hkv + rt.g) * D;
-    const long long stride = (long long)a.Hkv * D;
-    kvst.issue(lds_addr(sK), a.k + base, stride, j0, rt.tr.L - 1, wave);
-    kvst.issue(lds_addr(sV), a.v + base, stride, j0, rt.tr.L - 1, wave);
+  // Asynchronous staging of the BN keys from j0 on (j0 < L) of KV head g.
+  // Byte offsets are formed with one 32 x 32 -> 64 bit product: the copies
+  // stand at the head of every sub-tile, in front of all its products.
+  const uint32_t row_bytes = 2u * (uint32_t)a.Hkv * D;
+  const char* kbase = (const char*)uniform_ptr(a.k + ((long long)tr.tok0 * a.Hkv + rt.g) * D);
+  const char* vbase = (const char*)uniform_ptr(a.v + ((long long)tr.tok0 * a.Hkv + rt.g) * D);
+  const char* ebase = (const char*)uniform_ptr(a.evict + tr.tok0);
+  auto stage = [&](uint16_t* sK, uint16_t* sV, int* sE, int j0) __attribute__((always_inline)) {
+    const uint64_t off = (uint64_t)(uint32_t)j0 * row_bytes;
+    const int dr = tr.L - 1 - j0;
+    const uint32_t lim = FwdStager<D>::limit(dr, (long long)a.Hkv * D);
+    kvst.issue_at(lds_addr(sK), kbase + off, lim, wave);
+    kvst.issue_at(lds_addr(sV), vbase + off, lim, wave);
     if (wave == nw - 1) {
-      if (BN == kWave || lane < BN) stage_words(lds_addr(sE), a.evict + rt.tr.tok0, j0, rt.tr.L - 1, lane);
+      if (BN == kWave || lane < BN) stage_words_at(lds_addr(sE), ebase + 4u * (uint32_t)j0, dr, lane);
     }
   };
 
@@ -360,23 +366,9 @@ fwd_kernel(RowArgs a) {
   walker_load(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags);
   int kt = __builtin_amdgcn_readfirstlane(walker_next(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags));
   int2 kst = kt >= 0 ? walker_stats(w, kt) : make_int2(0, 0);
-  int sub = 0;
 
-  // One tile: prefetch the next tile into (nK, nV, nE), compute on (cK, cV, cE).
-  auto body = [&](const uint16_t* cK, const uint16_t* cV, const int* cE, uint16_t* nK, uint16_t* nV, int* nE) {
-    // The next tile's statistics come from the walker's registers (no memory
-    // access) and are used one iteration later.
-    int nkt = kt, nsub = sub + 1;
-    int2 nkst = kst;
-    // next 64-key tile once this one is done or its remaining keys lie past the trace end
-    // (a staged sub-tile must start inside the trace)
-    if (nsub == NSUB || kt * kKeyTile + nsub * BN >= tr.L) {
-      nkt = __builtin_amdgcn_readfirstlane(walker_next(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags));
-      nsub = 0;
-      if (nkt >= 0) nkst = walker_stats(w, nkt);
-    }
-    if (nkt >= 0) stage(nK, nV, nE, nkt, nsub);
-    const int j0 = kt * kKeyTile + sub * BN;
+  // The products and the softmax of the sub-tile of BN keys from j0 on.
+  auto compute = [&](const uint16_t* cK, const uint16_t* cV, const int* cE, int j0) __attribute__((always_inline)) {
     const int cls = adjust_class(tile_class(rt.i0w, rt.i0w + 32, j0, j0 + BN, tr.L, kst.x, kst.y), a.flags);
     if (cls != kEmpty) {
       f32x16 s[NKB];
@@ -435,20 +427,58 @@ fwd_kernel(RowArgs a) {
         }
       __builtin_amdgcn_s_setprio(0);
     }
-    wait_vm();
-    __syncthreads();
-    kt = nkt;
-    sub = nsub;
-    kst = nkst;
   };
 
-  if (kt >= 0) stage(sK0, sV0, sE0, kt, 0);
+  // Next key tile and its statistics, from the walker's registers (no memory
+  // access); called behind a sub-tile's products, so that its scalar work runs
+  // while the matrix core still has some of them to do.
+  int nkt = -1;
+  int2 nkst = make_int2(0, 0);
+  auto walk = [&]() __attribute__((always_inline)) {
+    nkt = __builtin_amdgcn_readfirstlane(walker_next(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags));
+    if (nkt >= 0) nkst = walker_stats(w, nkt);
+  };
+  const int jend = min(rt.i1, tr.L);   // no row of the workgroup sees a key from here on
+
+  if (kt >= 0) stage(sK0, sV0, sE0, kt * kKeyTile);
+  if (NSUB == 1 && kt >= 0) walk();
   wait_vm();
   __syncthreads();
   while (kt >= 0) {
-    body(sK0, sV0, sE0, sK1, sV1, sE1);
-    if (kt < 0) break;
-    body(sK1, sV1, sE1, sK0, sV0, sE0);
+    const int j0 = kt * kKeyTile;
+    if (NSUB == 2) {
+      // the two halves of a 64-key tile; where no row sees the second one it is the last tile
+      const bool second = j0 + BN < jend;
+      if (second) stage(sK1, sV1, sE1, j0 + BN);
+      compute(sK0, sV0, sE0, j0);
+      if (!second) break;
+      walk();
+      wait_vm();
+      __syncthreads();
+      if (nkt >= 0) stage(sK0, sV0, sE0, nkt * kKeyTile);
+      compute(sK1, sV1, sE1, j0 + BN);
+      if (nkt < 0) break;
+      kt = nkt;
+      kst = nkst;
+      wait_vm();
+      __syncthreads();
+    } else {
+      if (nkt >= 0) stage(sK1, sV1, sE1, nkt * kKeyTile);
+      compute(sK0, sV0, sE0, j0);
+      kt = nkt;
+      kst = nkst;
+      if (kt >= 0) walk();
+      wait_vm();
+      __syncthreads();
+      if (kt < 0) break;
+      if (nkt >= 0) stage(sK0, sV0, sE0, nkt * kKeyTile);
+      compute(sK1, sV1, sE1, kt * kKeyTile);
+      kt = nkt;
+      kst = nkst;
+      if (kt >= 0) walk();
+      wait_vm();
+      __syncthreads();
+    }
   }
 
   const float l_tot = l_run + wave_xor32(l_run);
