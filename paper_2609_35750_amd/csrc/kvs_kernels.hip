@@ -277,17 +277,6 @@ __device__ __forceinline__ bool row_tile(const RowArgs& a, RowTile& t) {
 template <int D>
 using KVStager = RowStager<D, kKeyTile, 4, true>;   // row kernels: 4 waves
 
-template <int D>
-__device__ __forceinline__ void stage_kv(const KVStager<D>& st, uint16_t* sK, uint16_t* sV, int* sE, const RowArgs& a,
-                                         const RowTile& rt, int kt, int wave, int nw, int lane) {
-  const int j0 = kt * kKeyTile;
-  const long long base = ((long long)rt.tr.tok0 * a.Hkv + rt.g) * D;
-  const long long stride = (long long)a.Hkv * D;
-  st.issue(lds_addr(sK), a.k + base, stride, j0, rt.tr.L - 1, wave);
-  st.issue(lds_addr(sV), a.v + base, stride, j0, rt.tr.L - 1, wave);
-  if (wave == nw - 1) stage_words(lds_addr(sE), a.evict + rt.tr.tok0, j0, rt.tr.L - 1, lane);
-}
-
 // ---------------------------------------------------------------- forward
 // K/V are staged in sub-tiles of BN keys (D = 128: 32, so that a workgroup
 // needs 37 KB of LDS and three workgroups, three waves per SIMD, share a CU;
@@ -550,6 +539,19 @@ __global__ void __launch_bounds__(512) dq_kernel(RowArgs a) {
   const int tl = Lay<D, true>::tr_lo(lane), th = Lay<D, true>::tr_hi(lane);
   KVStager<D> kvst;
   kvst.init(wave, lane, (long long)a.Hkv * D);
+  // asynchronous staging of the 64 keys from j0 on (j0 < L) of KV head g, as in the forward
+  const uint32_t row_bytes = 2u * (uint32_t)a.Hkv * D;
+  const char* kbase = (const char*)uniform_ptr(a.k + ((long long)tr.tok0 * a.Hkv + rt.g) * D);
+  const char* vbase = (const char*)uniform_ptr(a.v + ((long long)tr.tok0 * a.Hkv + rt.g) * D);
+  const char* ebase = (const char*)uniform_ptr(a.evict + tr.tok0);
+  auto stage = [&](uint16_t* sK, uint16_t* sV, int* sE, int j0) __attribute__((always_inline)) {
+    const uint64_t off = (uint64_t)(uint32_t)j0 * row_bytes;
+    const int dr = tr.L - 1 - j0;
+    const uint32_t lim = KVStager<D>::limit(dr, (long long)a.Hkv * D);
+    kvst.issue_at(lds_addr(sK), kbase + off, lim, wave);
+    kvst.issue_at(lds_addr(sV), vbase + off, lim, wave);
+    if (wave == nw - 1) stage_words_at(lds_addr(sE), ebase + 4u * (uint32_t)j0, dr, lane);
+  };
   const int ic = min(i, tr.L - 1);
 
   bf16x8 qreg[KS], oreg[KS];
@@ -576,15 +578,16 @@ __global__ void __launch_bounds__(512) dq_kernel(RowArgs a) {
   int kt = __builtin_amdgcn_readfirstlane(walker_next(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags));
   int2 kst = kt >= 0 ? walker_stats(w, kt) : make_int2(0, 0);
 
+  // The next tile and its statistics come from the walker's registers (no
+  // memory access), one tile ahead and behind the current tile's products.
+  int nkt = -1;
+  int2 nkst = make_int2(0, 0);
+  auto walk = [&]() __attribute__((always_inline)) {
+    nkt = __builtin_amdgcn_readfirstlane(walker_next(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags));
+    if (nkt >= 0) nkst = walker_stats(w, nkt);
+  };
   auto body = [&](const uint16_t* cK, const uint16_t* cV, const int* cE, uint16_t* nK, uint16_t* nV, int* nE) {
-    // The next tile's statistics come from the walker's registers (no memory
-    // access) and are used one iteration later.
-    const int nkt = __builtin_amdgcn_readfirstlane(walker_next(w, a.kstats, kidx0, rt.i0, rt.i1, tr.L, a.flags));
-    int2 nkst = make_int2(0, 0);
-    if (nkt >= 0) {
-      nkst = walker_stats(w, nkt);
-      stage_kv<D>(kvst, nK, nV, nE, a, rt, nkt, wave, nw, lane);
-    }
+    if (nkt >= 0) stage(nK, nV, nE, nkt * kKeyTile);
     const int j0 = kt * kKeyTile;
     const int cls = adjust_class(tile_class(rt.i0w, rt.i0w + 32, j0, j0 + kKeyTile, tr.L, kst.x, kst.y), a.flags);
     if (cls != kEmpty) {
@@ -611,13 +614,18 @@ __global__ void __launch_bounds__(512) dq_kernel(RowArgs a) {
         }
       }
     }
-    wait_vm();
-    __syncthreads();
     kt = nkt;
     kst = nkst;
+    if (kt < 0) return;   // the last tile: nothing staged, no buffer reused
+    walk();
+    wait_vm();
+    __syncthreads();
   };
 
-  if (kt >= 0) stage_kv<D>(kvst, sK0, sV0, sE0, a, rt, kt, wave, nw, lane);
+  if (kt >= 0) {
+    stage(sK0, sV0, sE0, kt * kKeyTile);
+    walk();
+  }
   wait_vm();
   __syncthreads();
   while (kt >= 0) {
