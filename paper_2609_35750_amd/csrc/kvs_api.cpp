@@ -87,7 +87,7 @@ kvs_status_t check_ws(void* ws, size_t have, size_t need) {
 kvs_status_t run_fwd(kvs::Problem& p) {
   head_grouping(p);
   int2* kstats = (int2*)p.ws;
-  hipError_t e = kvs::launch_kstats(p, 64, kstats);
+  hipError_t e = kvs::launch_kstats(p, kstats);
   if (e != hipSuccess) return hip_fail(e, "key-tile statistics launch");
   e = kvs::launch_fwd(p, kstats);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
@@ -98,9 +98,7 @@ kvs_status_t run_bwd(kvs::Problem& p) {
   head_grouping(p);
   int2* kstats = (int2*)p.ws;
   float* delta = (float*)((char*)p.ws + kvs::ws_kstats_bytes(p.B, p.ntok));
-  hipError_t e = kvs::launch_kstats(p, 64, kstats);
-  if (e != hipSuccess) return hip_fail(e, "key-tile statistics launch");
-  e = kvs::launch_bwd_pre(p, delta);
+  hipError_t e = kvs::launch_bwd_pre(p, kstats, delta);
   if (e != hipSuccess) return hip_fail(e, "backward preprocess launch");
   void* split_ws = (char*)delta + kvs::ws_delta_bytes(p.Hq, p.ntok);
   e = kvs::launch_bwd_dkdv(p, kstats, delta, split_ws);

@@ -147,16 +147,18 @@ __device__ __forceinline__ int wave_scan(int x) {
   return x;
 }
 __device__ __forceinline__ int wave_last(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
-// Largest value over the 64 lanes (x >= 0).
-__device__ __forceinline__ int wave_max(int x) {
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
-  return wave_last(x);
-}
+// Largest and smallest value over the 64 lanes (a lane without a source keeps its own).
+#define KVS_WAVE_FOLD(op)                                                       \
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));         \
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));         \
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));         \
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));         \
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));         \
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));         \
+  return wave_last(x)
+__device__ __forceinline__ int wave_max(int x) { KVS_WAVE_FOLD(max); }
+__device__ __forceinline__ int wave_min(int x) { KVS_WAVE_FOLD(min); }
+#undef KVS_WAVE_FOLD
 
 // Asynchronous global -> LDS copy (global_load_lds_dword{,x4}): lane l of the
 // wave writes its 4 or 16 bytes at LDS byte address lds + (4 or 16) l.  Issued

@@ -63,7 +63,7 @@ struct ColArgs {
   uint16_t* dk;
   uint16_t* dv;
   const int* plan;      // [B * nkt][2]: parts of the key block (1 = not split), first slot
-  const int2* items;    // [B * nkt + capE]: (key block, part) work items, longest first
+  const int2* items;    // [B * nkt + capE]: (key block, part) work items, longest first; NULL: one per key block
   int* ctl;             // PlanCtl
   float* part;          // [capE * Hkv][2][kColKeys][D] fp32 partial dV, dK of split blocks
   int B, T, Hq, Hkv, G, nkt, ntok;
@@ -110,14 +110,25 @@ __device__ __forceinline__ int2 key_tile_stats(const int* __restrict__ evict, co
   return make_int2(mn, mx);
 }
 
-// One thread per (trace, key tile of BN keys).
-__global__ void __launch_bounds__(64) kstats_kernel(const int* __restrict__ evict, const int* __restrict__ cu,
-                                                    int T, int ntok, int BN, int2* __restrict__ out) {
-  const int kt = blockIdx.x * kWave + threadIdx.x, b = blockIdx.y;
+// Statistics of the 64-key tiles of all traces: one wave a tile, one lane a
+// key, four tiles a workgroup of 256 threads (group wg of tg per trace).  Bound
+// by one memory latency; one thread a tile walked its 64 keys in series, 6.0 us
+// for 512 tokens and 7.4 for 8,191, against 2.3 and 4.6 (a launch's own time).
+__device__ __forceinline__ void kstats_group(const int* __restrict__ evict, const int* __restrict__ cu, int T, int ntok,
+                                             int wg, int tg, int2* __restrict__ out) {
+  const int b = wg / tg, kt = (wg - b * tg) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   const Trace tr = trace_of(cu, b, T, ntok);
-  const int j0 = kt * BN;
+  const int j0 = kt * kKeyTile;
   if (j0 >= tr.L) return;
-  out[kstat_index(b, tr.tok0, kt, BN)] = key_tile_stats(evict, tr, j0, BN);
+  const int e = min(evict[tr.tok0 + min(j0 + lane, tr.L - 1)], tr.L);   // lanes past the end repeat the last key
+  const int mn = wave_min(e), mx = wave_max(e);
+  if (lane == 0) out[kstat_index(b, tr.tok0, kt, kKeyTile)] = make_int2(mn, mx);
+}
+__host__ __device__ __forceinline__ int kstats_groups(int T) { return ((T + kKeyTile - 1) / kKeyTile + 3) / 4; }
+
+__global__ void __launch_bounds__(256) kstats_kernel(const int* __restrict__ evict, const int* __restrict__ cu, int T,
+                                                     int ntok, int2* __restrict__ out) {
+  kstats_group(evict, cu, T, ntok, blockIdx.x, kstats_groups(T), out);
 }
 
 // ---------------------------------------------------------------- tile-class grid
@@ -489,13 +500,21 @@ fwd_kernel(RowArgs a) {
 
 // ---------------------------------------------------------------- backward: Delta = rowsum(dO * O), stored as -Delta
 // Also writes LSE * log2(e), the form in which the backward kernels use it.
+// The first nks workgroups take the key-tile statistics instead (a launch less
+// ahead of the backward's main kernels).
 template <int D>
 __global__ void __launch_bounds__(256) bwd_pre_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout,
                                                       const float* __restrict__ lse, float* __restrict__ delta,
-                                                      float* __restrict__ lse2, int ntok, int Hq, int T, int varlen) {
+                                                      float* __restrict__ lse2, int ntok, int Hq, int T, int varlen,
+                                                      const int* __restrict__ evict, const int* __restrict__ cu,
+                                                      int nks, int2* __restrict__ kstats) {
+  if ((int)blockIdx.x < nks) {
+    kstats_group(evict, cu, T, ntok, blockIdx.x, kstats_groups(T), kstats);
+    return;
+  }
   constexpr int PER = D / 16;  // elements per lane, 16 lanes per row
   const int sub = threadIdx.x & 15;
-  const long long row = (long long)blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);
+  const long long row = (long long)(blockIdx.x - nks) * (blockDim.x / 16) + (threadIdx.x >> 4);
   const bool ok = row < (long long)ntok * Hq;
   float s = 0.f;
   if (ok) {
@@ -695,16 +714,18 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // ended in turn behind the last items, as many as there are unused slots.)
   PlanCtl* ctl = reinterpret_cast<PlanCtl*>(a.ctl);
   const int nq = queue_count(a.Hkv), queue = nq > 1 ? blockIdx.x % a.Hkv : 0;
-  const int nidx = nq > 1 ? ctl->nitems : ctl->nitems * a.Hkv;
+  const int nitems = a.items ? ctl->nitems : a.B * a.nkt;
+  const int nidx = nq > 1 ? nitems : nitems * a.Hkv;
   int idx = nq > 1 ? blockIdx.x / a.Hkv : blockIdx.x;
   const bool more = (int)gridDim.x / nq < nidx;   // items beyond the first ones
   while (idx < nidx) {
   const int g = nq > 1 ? queue : idx % a.Hkv;
-  const int2 item = a.items[nq > 1 ? idx : idx / a.Hkv];
+  const int2 item = a.items ? a.items[nq > 1 ? idx : idx / a.Hkv] : make_int2(nq > 1 ? idx : idx / a.Hkv, 0);
   const int b = item.x / a.nkt, kt = item.x % a.nkt, chunk = item.y;
-  const int nchunk = a.plan[2 * item.x], slot0 = a.plan[2 * item.x + 1];
+  const int nchunk = a.items ? a.plan[2 * item.x] : 1, slot0 = a.items ? a.plan[2 * item.x + 1] : 0;
   const Trace tr = trace_of(a.cu, b, a.T, a.ntok);
-  const int j0 = kt * kColKeys;   // < tr.L: the plan lists no block past its trace
+  const int j0 = kt * kColKeys;
+  if (j0 >= tr.L) break;   // only without a plan, where every workgroup has one item; the plan lists no such block
   // per-lane constants are recomputed for every item: held across items they cost registers the loop lacks
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
@@ -1370,10 +1391,13 @@ static RowArgs row_args(const Problem& p, const int2* kstats) {
   return a;
 }
 
-hipError_t launch_kstats(const Problem& p, int BN, int2* kstats) {
-  dim3 grid(((p.T + BN - 1) / BN + kWave - 1) / kWave, p.B);
+constexpr int kMaxTraces = 65535;   // keeps every grid and workgroup index within 31 bits
+
+hipError_t launch_kstats(const Problem& p, int2* kstats) {
+  if (p.B > kMaxTraces) return hipErrorInvalidConfiguration;
   prof_begin("classify", p.stream);
-  hipLaunchKernelGGL(kstats_kernel, grid, dim3(kWave), 0, p.stream, p.evict, p.cu, p.T, p.ntok, BN, kstats);
+  hipLaunchKernelGGL(kstats_kernel, dim3((unsigned)((long long)kstats_groups(p.T) * p.B)), dim3(256), 0, p.stream,
+                     p.evict, p.cu, p.T, p.ntok, kstats);
   prof_end(p.stream);
   return hipGetLastError();
 }
@@ -1389,17 +1413,21 @@ hipError_t launch_fwd(const Problem& p, const int2* kstats) {
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_pre(const Problem& p, float* delta) {
+hipError_t launch_bwd_pre(const Problem& p, int2* kstats, float* delta) {
+  if (p.B > kMaxTraces) return hipErrorInvalidConfiguration;
   const long long rows = (long long)p.ntok * p.Hq;
   float* lse2 = (float*)((char*)delta + half_delta_bytes(p.Hq, p.ntok));
-  dim3 grid((unsigned)((rows + 15) / 16)), block(256);
+  const int nks = kstats_groups(p.T) * p.B;
+  dim3 grid((unsigned)((rows + 15) / 16 + nks)), block(256);
   prof_begin("bwd_pre", p.stream);
   if (p.D == 128)
     hipLaunchKernelGGL(bwd_pre_kernel<128>, grid, block, 0, p.stream, (const uint16_t*)p.o_in,
-                       (const uint16_t*)p.dout, p.lse_in, delta, lse2, p.ntok, p.Hq, p.T, (int)(p.cu != nullptr));
+                       (const uint16_t*)p.dout, p.lse_in, delta, lse2, p.ntok, p.Hq, p.T, (int)(p.cu != nullptr),
+                       p.evict, p.cu, nks, kstats);
   else
     hipLaunchKernelGGL(bwd_pre_kernel<64>, grid, block, 0, p.stream, (const uint16_t*)p.o_in,
-                       (const uint16_t*)p.dout, p.lse_in, delta, lse2, p.ntok, p.Hq, p.T, (int)(p.cu != nullptr));
+                       (const uint16_t*)p.dout, p.lse_in, delta, lse2, p.ntok, p.Hq, p.T, (int)(p.cu != nullptr),
+                       p.evict, p.cu, nks, kstats);
   prof_end(p.stream);
   return hipGetLastError();
 }
@@ -1441,10 +1469,12 @@ hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* de
     w += round256(sizeof(PlanCtl));
     split = (int*)w;
     w += round256((size_t)a.capE * sizeof(int));
-    a.plan = plan;
-    a.items = items;
     a.part = (float*)w;
-    hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, p.stream, kstats, p.cu, p.B, p.T, p.ntok, a.nkt,
+    // Without parts, and where every block starts at once, there is nothing to plan (5 us, and a launch).
+    if (a.capE == 0 && (long long)p.B * a.nkt * p.Hkv <= grid) plan = nullptr;
+    a.plan = plan;
+    a.items = plan ? items : nullptr;
+    if (plan) hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, p.stream, kstats, p.cu, p.B, p.T, p.ntok, a.nkt,
                        p.G, p.Hkv, a.capE, grid, plan, items, split, (PlanCtl*)a.ctl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -45,9 +45,9 @@ size_t ws_delta_bytes(int Hq, int ntok);
 size_t ws_split_bytes(int B, int T, int Hkv, int G, int D);
 
 // Launchers.  Each returns the hipError_t of its launch(es).
-hipError_t launch_kstats(const Problem& p, int BN, int2* kstats);
+hipError_t launch_kstats(const Problem& p, int2* kstats);
 hipError_t launch_fwd(const Problem& p, const int2* kstats);
-hipError_t launch_bwd_pre(const Problem& p, float* delta);
+hipError_t launch_bwd_pre(const Problem& p, int2* kstats, float* delta);   // and the key-tile statistics
 hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* delta, void* split_ws);
 hipError_t launch_bwd_dq(const Problem& p, const int2* kstats, const float* delta);
 hipError_t launch_classify(const int32_t* evict, const int32_t* cu, int B, int T, int BM, int BN,

@@ -291,11 +291,13 @@ class _EvictAttn(torch.autograd.Function):
         ctx.save_for_backward(q, k, v, o, lse, evict_at, cu_seqlens)
         ctx.scale, ctx.max_seqlen = scale, max_seqlen
         ctx.mark_non_differentiable(lse)
+        ctx.set_materialize_grads(False)   # LSE carries no gradient: no zeros filled for it
         return o, lse
 
     @staticmethod
     def backward(ctx, do, _dlse):
         q, k, v, o, lse, evict_at, cu_seqlens = ctx.saved_tensors
+        do = torch.zeros_like(o) if do is None else do
         dq, dk, dv = kvs_evict_attn_bwd(do.contiguous(), q, k, v, o, lse, evict_at, ctx.scale, cu_seqlens,
                                         ctx.max_seqlen)
         return dq, dk, dv, None, None, None, None
