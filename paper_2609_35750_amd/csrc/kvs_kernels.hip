@@ -1091,25 +1091,25 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   if (threadIdx.x == 0) sNext = more ? atomicAdd(&ctl->next[queue], 1) : nidx;
   if (nchunk > 1) {
-    // fp32 partial sums of this chunk: [slot][dV, dK][key in block][d]
-    float* dst = a.part + (((size_t)(slot0 + chunk) * a.Hkv + g) * 2 + (role_dk ? 1 : 0)) * kColKeys * D +
-                 (size_t)(32 * kw + col) * D;
+    // fp32 partial sums of this part: [slot][dV, dK][32-key group], each group
+    // as the accumulators lie, [d][q4][lane][4], so that a store instruction
+    // writes 1 KB in a row (split_reduce_kernel turns the sums)
+    float* dst = a.part + ((((size_t)(slot0 + chunk) * a.Hkv + g) * 2 + (role_dk ? 1 : 0)) * 4 + kw) * 32 * D + 4 * lane;
 #pragma unroll
     for (int d = 0; d < DB; ++d)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
-        *reinterpret_cast<float4*>(dst + 32 * d + 8 * q4 + 4 * half) =
+        *reinterpret_cast<float4*>(dst + (4 * d + q4) * 4 * kWave) =
             make_float4(acc[d][4 * q4], acc[d][4 * q4 + 1], acc[d][4 * q4 + 2], acc[d][4 * q4 + 3]);
-  } else if (key_ok) {
-    const size_t koff = ((size_t)(tr.tok0 + j) * a.Hkv + g) * D;
-    uint16_t* dst = role_dk ? a.dk + koff : a.dv + koff;
-    const float sc = role_dk ? a.scale : 1.f;
+  } else {
+    // whole rows through LDS: every wave has its own buffer among the tiles', which are free
+    uint16_t* const bufs[8] = {sQ0, sQ1, sQ2, sO0, sO1, sO2, (uint16_t*)sP, (uint16_t*)(sP + 4 * 2 * 2 * kWave)};
+    uint16_t* buf = bufs[0];
 #pragma unroll
-    for (int d = 0; d < DB; ++d)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        *reinterpret_cast<uint2*>(dst + 32 * d + 8 * q4 + 4 * half) =
-            pack4_bf16(acc[d][4 * q4] * sc, acc[d][4 * q4 + 1] * sc, acc[d][4 * q4 + 2] * sc, acc[d][4 * q4 + 3] * sc);
+    for (int w = 1; w < 8; ++w) buf = wave == w ? bufs[w] : buf;
+    store_rows<D>(acc, role_dk ? a.scale : 1.f, buf,
+                  (role_dk ? a.dk : a.dv) + ((size_t)(tr.tok0 + jw0) * a.Hkv + g) * D, (long long)a.Hkv * D, tr.L - jw0,
+                  lane);
   }
   __syncthreads();   // sNext; and every wave is done with the LDS of this item
   idx = __builtin_amdgcn_readfirstlane(sNext);
@@ -1251,9 +1251,10 @@ __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict
 }
 
 // Sum of the parts' partials of split key blocks, in part order; dK scaled.
-// The split blocks are listed by the plan, and a fixed grid walks the float4
-// slices of 256 threads of all of them (dV and dK): bound by reading the
-// partials, so every thread keeps several parts' loads in flight.
+// The split blocks are listed by the plan, and a fixed grid walks the 32-key
+// groups of dV and dK of all of them.  Bound by reading the partials, so every
+// thread keeps several parts' loads in flight; the sums are turned in LDS and
+// stored as whole rows.
 constexpr int kReduceGrid = 2048;
 template <int D>
 __global__ void __launch_bounds__(256) split_reduce_kernel(const PlanCtl* __restrict__ ctl,
@@ -1261,44 +1262,49 @@ __global__ void __launch_bounds__(256) split_reduce_kernel(const PlanCtl* __rest
                                                            const float* __restrict__ part, const int* __restrict__ cu,
                                                            uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int B,
                                                            int T, int ntok, int nkt, int Hkv, float scale) {
-  constexpr int kSlices = 2 * kColKeys * D / 4 / 256;   // slices of one block and KV head; the first half is dV
+  constexpr int P = D + 8, NF = D / 32;              // LDS row pitch; float4s of a thread: fragments of 256
   constexpr size_t kSlot = (size_t)2 * kColKeys * D;    // floats of one slot
-  const int tasks = ctl->nsplit * Hkv * kSlices;
+  __shared__ __attribute__((aligned(16))) uint16_t buf[32 * P];
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+  const int tasks = ctl->nsplit * Hkv * 8;
   for (int t = blockIdx.x; t < tasks; t += gridDim.x) {
-    const int slice = t % kSlices, bg = t / kSlices, g = bg % Hkv, blk = split[bg / Hkv];
+    const int grp = t & 7, bg = t >> 3, g = bg % Hkv, blk = split[bg / Hkv];   // group: dV 0..3, dK 4..7
     const int nc = plan[2 * blk], s0 = plan[2 * blk + 1];
     const int b = blk / nkt, kt = blk % nkt;
-    const int e = (slice * 256 + threadIdx.x) * 4;   // element of [dV, dK][key][d]
-    const float* src = part + ((size_t)s0 * Hkv + g) * kSlot + e;
-    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-    int c = 0;
-    for (; c + 4 <= nc; c += 4) {
-      float4 v[4];
+    const float* src = part + ((size_t)s0 * Hkv + g) * kSlot + (size_t)grp * 32 * D + 4 * tid;
+    float4 sum[NF];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(src + (size_t)(c + k) * Hkv * kSlot);
+    for (int n = 0; n < NF; ++n) sum[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 2
+    for (int c = 0; c < nc; ++c) {
+      float4 v[NF];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        sum.x += v[k].x;
-        sum.y += v[k].y;
-        sum.z += v[k].z;
-        sum.w += v[k].w;
+      for (int n = 0; n < NF; ++n) v[n] = *reinterpret_cast<const float4*>(src + (size_t)c * Hkv * kSlot + n * 1024);
+#pragma unroll
+      for (int n = 0; n < NF; ++n) {
+        sum[n].x += v[n].x;
+        sum[n].y += v[n].y;
+        sum[n].z += v[n].z;
+        sum[n].w += v[n].w;
       }
     }
-    for (; c < nc; ++c) {
-      const float4 v = *reinterpret_cast<const float4*>(src + (size_t)c * Hkv * kSlot);
-      sum.x += v.x;
-      sum.y += v.y;
-      sum.z += v.z;
-      sum.w += v.w;
-    }
-    const int which = e / (kColKeys * D), key = e / D % kColKeys, d = e % D;
+    const float sc = grp >= 4 ? scale : 1.f;
+    // float4 n of wave w is fragment 4 n + w: columns 32 n + 8 w + 4 half of key `col`
+#pragma unroll
+    for (int n = 0; n < NF; ++n)
+      *reinterpret_cast<uint2*>(buf + col * P + 32 * n + 8 * (tid >> 6) + 4 * half) =
+          pack4_bf16(sum[n].x * sc, sum[n].y * sc, sum[n].z * sc, sum[n].w * sc);
+    asm volatile("" ::: "memory");   // the same bytes are read back as another type
+    __syncthreads();
     const Trace tr = trace_of(cu, b, T, ntok);
-    const int j = kt * kColKeys + key;
-    if (j < tr.L) {
-      const float sc = which ? scale : 1.f;
-      uint16_t* dst = (which ? dk : dv) + ((size_t)(tr.tok0 + j) * Hkv + g) * D + d;
-      *reinterpret_cast<uint2*>(dst) = pack4_bf16(sum.x * sc, sum.y * sc, sum.z * sc, sum.w * sc);
+    constexpr int LPR = D / 8;
+#pragma unroll
+    for (int n = 0; n < 32 * LPR / 256; ++n) {
+      const int r = (n * 256 + tid) / LPR, c = 8 * (tid % LPR), j = kt * kColKeys + 32 * (grp & 3) + r;
+      const uint4 v = *reinterpret_cast<const uint4*>(buf + r * P + c);
+      if (j < tr.L) *reinterpret_cast<uint4*>((grp >= 4 ? dk : dv) + ((size_t)(tr.tok0 + j) * Hkv + g) * D + c) = v;
     }
+    __syncthreads();
   }
 }
 
