@@ -1089,7 +1089,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (role_dk) run(std::true_type{});
   else run(std::false_type{});
 
-  if (threadIdx.x == 0) sNext = more ? atomicAdd(&ctl->next[queue], 1) : nidx;
+  int next = nidx;   // asked for ahead of the stores, waited for behind them
+  if (threadIdx.x == 0 && more) next = atomicAdd(&ctl->next[queue], 1);
   if (nchunk > 1) {
     // fp32 partial sums of this part: [slot][dV, dK][32-key group], each group
     // as the accumulators lie, [d][q4][lane][4], so that a store instruction
@@ -1111,6 +1112,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                   (role_dk ? a.dk : a.dv) + ((size_t)(tr.tok0 + jw0) * a.Hkv + g) * D, (long long)a.Hkv * D, tr.L - jw0,
                   lane);
   }
+  if (threadIdx.x == 0) sNext = next;
   __syncthreads();   // sNext; and every wave is done with the LDS of this item
   idx = __builtin_amdgcn_readfirstlane(sNext);
   }
