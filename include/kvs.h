@@ -314,6 +314,18 @@ kvs_status_t kvs_paged_append(const void* K_new, const void* V_new, const int32_
 kvs_status_t kvs_paged_evict(const int32_t* slots, int n, int32_t* slot_pos, int num_blocks, int block_size,
                              void* stream);
 
+/* The same updates from HOST lists of positions and slots (the ones kvs_bm_append
+ * and kvs_bm_evict give), which are read before the call returns: the slots
+ * travel as runs in the launch's arguments and nothing is uploaded.  Lists
+ * that lie in too many runs (more than 512; consecutive slots up or down, and
+ * for the append consecutive positions, make a run) give KVS_ERR_UNSUPPORTED
+ * before any work is enqueued: use the calls above. */
+kvs_status_t kvs_paged_append_host(const void* K_new, const void* V_new, const int32_t* positions,
+                                   const int32_t* slots, int n, void* K_cache, void* V_cache, int32_t* slot_pos,
+                                   int num_blocks, int block_size, int Hkv, int D, void* stream);
+kvs_status_t kvs_paged_evict_host(const int32_t* slots, int n, int32_t* slot_pos, int num_blocks, int block_size,
+                                  void* stream);
+
 /* ---- decode attention over the live cache
  * One query token per sequence: Q, O bf16 [num_seqs][Hq][D], LSE fp32
  * [num_seqs][Hq] (natural log).  Sequence s attends over every slot of its

@@ -519,6 +519,78 @@ kvs_status_t kvs_paged_evict(const int32_t* slots, int n, int32_t* slot_pos, int
   return e == hipSuccess ? KVS_OK : hip_fail(e, "paged evict launch");
 }
 
+// The next runs of a host slot list from token t on (at most kMaxRuns); pos may be NULL (eviction).
+static void next_runs(const int32_t* pos, const int32_t* slots, int n, int* t, kvs::SlotRuns* out) {
+  out->n = 0;
+  int i = *t;
+  while (i < n && out->n < kvs::kMaxRuns) {
+    const int first = i++;
+    int step = 0;   // of the run, once it has two tokens
+    for (; i < n; ++i) {
+      const long long d = (long long)slots[i] - slots[i - 1];
+      if ((d != 1 && d != -1) || (step != 0 && d != step)) break;
+      if (pos && (long long)pos[i] - pos[i - 1] != 1) break;
+      step = (int)d;
+    }
+    out->r[out->n++] = {first, slots[first], pos ? pos[first] : 0, step < 0 ? -(i - first) : i - first};
+  }
+  *t = i;
+}
+
+// Launches a list may take: beyond, one upload costs less than the launches (an upload and its wait take about 15
+// us, a launch 5).
+constexpr int kMaxRunLaunches = 4;
+
+static bool count_runs(const int32_t* pos, const int32_t* slots, int n) {
+  kvs::SlotRuns runs;
+  int t = 0;
+  for (int k = 0; k < kMaxRunLaunches && t < n; ++k) next_runs(pos, slots, n, &t, &runs);
+  return t == n;
+}
+
+kvs_status_t kvs_paged_append_host(const void* K_new, const void* V_new, const int32_t* positions,
+                                   const int32_t* slots, int n, void* K_cache, void* V_cache, int32_t* slot_pos,
+                                   int num_blocks, int block_size, int Hkv, int D, void* stream) {
+  t_err.clear();
+  if (kvs_status_t st = check_cache_dims(num_blocks, block_size)) return st;
+  if (n < 0 || Hkv < 1) return fail(KVS_ERR_SHAPE, "n must be >= 0 and Hkv >= 1");
+  if (D != 64 && D != 128) return fail(KVS_ERR_SHAPE, "head dim D must be 64 or 128 (got %d)", D);
+  REQUIRE_PTR(K_cache, "K_cache");
+  REQUIRE_PTR(V_cache, "V_cache");
+  if (!slot_pos) return fail(KVS_ERR_NULL, "slot_pos is NULL");
+  if (n == 0) return KVS_OK;
+  REQUIRE_PTR(K_new, "K_new");
+  REQUIRE_PTR(V_new, "V_new");
+  if (!positions || !slots) return fail(KVS_ERR_NULL, "positions or slots is NULL");
+  if (!count_runs(positions, slots, n)) return fail(KVS_ERR_UNSUPPORTED, "slots lie in too many runs");
+  kvs::SlotRuns runs;
+  for (int t = 0; t < n;) {
+    next_runs(positions, slots, n, &t, &runs);
+    hipError_t e = kvs::launch_paged_append_runs(K_new, V_new, runs, K_cache, V_cache, slot_pos,
+                                                 num_blocks * block_size, block_size, Hkv, D, (hipStream_t)stream);
+    if (e != hipSuccess) return hip_fail(e, "paged append launch");
+  }
+  return KVS_OK;
+}
+
+kvs_status_t kvs_paged_evict_host(const int32_t* slots, int n, int32_t* slot_pos, int num_blocks, int block_size,
+                                  void* stream) {
+  t_err.clear();
+  if (kvs_status_t st = check_cache_dims(num_blocks, block_size)) return st;
+  if (n < 0) return fail(KVS_ERR_SHAPE, "n must be >= 0");
+  if (!slot_pos) return fail(KVS_ERR_NULL, "slot_pos is NULL");
+  if (n == 0) return KVS_OK;
+  if (!slots) return fail(KVS_ERR_NULL, "slots is NULL");
+  if (!count_runs(nullptr, slots, n)) return fail(KVS_ERR_UNSUPPORTED, "slots lie in too many runs");
+  kvs::SlotRuns runs;
+  for (int t = 0; t < n;) {
+    next_runs(nullptr, slots, n, &t, &runs);
+    hipError_t e = kvs::launch_paged_evict_runs(runs, slot_pos, num_blocks * block_size, (hipStream_t)stream);
+    if (e != hipSuccess) return hip_fail(e, "paged evict launch");
+  }
+  return KVS_OK;
+}
+
 static kvs_status_t check_decode_dims(int S, int Hq, int Hkv, int D, int num_blocks, int block_size,
                                       int max_blocks) {
   if (S < 1 || Hq < 1 || Hkv < 1 || max_blocks < 1)

@@ -11,9 +11,50 @@
 
 #include <algorithm>
 #include <cstdio>
-#include <unordered_set>
 
 namespace kvs {
+
+SlotMap::Page* SlotMap::page(int idx) {
+  if (idx == last_idx_) return last_;
+  const auto it = pages_.find(idx);
+  if (it == pages_.end()) return nullptr;
+  last_idx_ = idx;
+  return last_ = it->second.get();
+}
+
+int* SlotMap::make(int pos) {
+  const int idx = pos >> kBits;
+  Page* p = page(idx);
+  if (!p) {
+    auto fresh = std::make_unique<Page>();
+    for (int& s : fresh->slot) s = kNone;
+    p = fresh.get();
+    pages_.emplace(idx, std::move(fresh));
+    last_idx_ = idx;
+    last_ = p;
+  }
+  return &p->slot[pos & kMask];
+}
+
+void SlotMap::count(int pos, int d) {
+  const int idx = pos >> kBits;
+  Page* p = page(idx);
+  if (!p) return;
+  p->live += d;
+  live_ += d;
+  if (p->live == 0) {
+    pages_.erase(idx);
+    last_idx_ = -1;
+    last_ = nullptr;
+  }
+}
+
+void SlotMap::clear() {
+  pages_.clear();
+  last_idx_ = -1;
+  last_ = nullptr;
+  live_ = 0;
+}
 
 BlockManager::BlockManager(int num_blocks, int block_size, int num_seqs, int max_blocks)
     : nb_(num_blocks), bs_(block_size), ns_(num_seqs), mb_(max_blocks),
@@ -34,18 +75,38 @@ static int fail_msg(std::string* err, int code, const char* msg, long long a = 0
 int BlockManager::append(int seq, const int32_t* pos, int n, int32_t* slots, std::string* err) {
   if (seq < 0 || seq >= ns_) return fail_msg(err, kBadArg, "sequence index %lld out of range", seq);
   auto& map = slot_of_[seq];
-  std::unordered_set<int> seen;
-  for (int i = 0; i < n; ++i) {
-    if (pos[i] < 0) return fail_msg(err, kBadArg, "negative trace position %lld", pos[i]);
-    if (map.count(pos[i]) || !seen.insert(pos[i]).second)
-      return fail_msg(err, kBadState, "trace position %lld is already in the cache", pos[i]);
+  // Reserve every position first (a marker no slot has), counted as live so that its page stays; a failure
+  // takes the markers back.
+  constexpr int kReserved = -2;
+  int done = 0, code = kOk;
+  for (; done < n; ++done) {
+    const int p = pos[done];
+    if (p < 0) {
+      code = fail_msg(err, kBadArg, "negative trace position %lld", p);
+      break;
+    }
+    int* s = map.make(p);
+    if (*s != SlotMap::kNone) {
+      code = fail_msg(err, kBadState, "trace position %lld is already in the cache", p);
+      break;
+    }
+    *s = kReserved;
+    map.count(p, 1);
   }
-  // blocks this append needs, checked before anything changes
+  // blocks this append needs, checked before anything else changes
   const int room = bs_ - tail_fill_[seq];
   const long long need = n > room ? (n - room + bs_ - 1) / bs_ : 0;
-  if (need > (long long)free_.size()) return fail_msg(err, kCapacity, "out of cache blocks (%lld more needed)", need);
-  if ((long long)blocks_[seq].size() + need > mb_)
-    return fail_msg(err, kCapacity, "sequence would hold more than max_blocks (%lld) blocks", mb_);
+  if (code == kOk && need > (long long)free_.size())
+    code = fail_msg(err, kCapacity, "out of cache blocks (%lld more needed)", need);
+  if (code == kOk && (long long)blocks_[seq].size() + need > mb_)
+    code = fail_msg(err, kCapacity, "sequence would hold more than max_blocks (%lld) blocks", mb_);
+  if (code != kOk) {
+    for (int i = 0; i < done; ++i) {
+      *map.find(pos[i]) = SlotMap::kNone;
+      map.count(pos[i], -1);
+    }
+    return code;
+  }
   for (int i = 0; i < n; ++i) {
     if (tail_fill_[seq] == bs_) {
       blocks_[seq].push_back(free_.back());
@@ -55,7 +116,7 @@ int BlockManager::append(int seq, const int32_t* pos, int n, int32_t* slots, std
     const int blk = blocks_[seq].back();
     const int slot = blk * bs_ + tail_fill_[seq]++;
     ++live_[blk];
-    map[pos[i]] = slot;
+    *map.find(pos[i]) = slot;
     slots[i] = slot;
   }
   return kOk;
@@ -72,15 +133,29 @@ void BlockManager::drop_block(int seq, int blk) {
 int BlockManager::evict(int seq, const int32_t* pos, int n, int32_t* slots, std::string* err) {
   if (seq < 0 || seq >= ns_) return fail_msg(err, kBadArg, "sequence index %lld out of range", seq);
   auto& map = slot_of_[seq];
-  std::unordered_set<int> seen;
+  // Mark every entry as taken first (its slot s >= 0 as kTaken - s), so that a repeated position shows; a failure
+  // takes the marks back.
+  constexpr int kTaken = -3;
   for (int i = 0; i < n; ++i) {
-    if (!map.count(pos[i])) return fail_msg(err, kBadState, "trace position %lld is not in the cache", pos[i]);
-    if (!seen.insert(pos[i]).second) return fail_msg(err, kBadState, "trace position %lld evicted twice", pos[i]);
+    int* s = pos[i] < 0 ? nullptr : map.find(pos[i]);
+    if (!s || *s < 0) {
+      const int code = s && *s <= kTaken
+                           ? fail_msg(err, kBadState, "trace position %lld evicted twice", pos[i])
+                           : fail_msg(err, kBadState, "trace position %lld is not in the cache", pos[i]);
+      while (--i >= 0) {
+        int* t = map.find(pos[i]);
+        *t = kTaken - *t;
+      }
+      return code;
+    }
+    *s = kTaken - *s;
   }
   for (int i = 0; i < n; ++i) {
-    auto it = map.find(pos[i]);
-    const int slot = it->second;
-    map.erase(it);
+    const int p = pos[i];
+    int* s = map.find(p);
+    const int slot = kTaken - *s;
+    *s = SlotMap::kNone;
+    map.count(p, -1);
     slots[i] = slot;
     const int blk = slot / bs_;
     if (--live_[blk] == 0) drop_block(seq, blk);
@@ -91,7 +166,7 @@ int BlockManager::evict(int seq, const int32_t* pos, int n, int32_t* slots, std:
 int BlockManager::release(int seq, int32_t* slots, int* n_slots, std::string* err) {
   if (seq < 0 || seq >= ns_) return fail_msg(err, kBadArg, "sequence index %lld out of range", seq);
   int k = 0;
-  for (const auto& kv : slot_of_[seq]) slots[k++] = kv.second;
+  slot_of_[seq].each([&](int slot) { slots[k++] = slot; });
   std::sort(slots, slots + k);
   *n_slots = k;
   slot_of_[seq].clear();
@@ -113,7 +188,7 @@ void BlockManager::tables(int32_t* block_table, int32_t* seq_blocks) const {
 }
 
 int BlockManager::live(int seq) const {
-  return (seq >= 0 && seq < ns_) ? (int)slot_of_[seq].size() : -1;
+  return (seq >= 0 && seq < ns_) ? slot_of_[seq].live() : -1;
 }
 
 }  // namespace kvs

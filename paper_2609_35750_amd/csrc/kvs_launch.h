@@ -70,6 +70,19 @@ struct PagedDecode {
   void* ws;
   hipStream_t stream;
 };
+// Slots of a host-held list as runs: |len| tokens from `tok` on, positions pos, pos + 1, ..., slots slot, slot + 1,
+// ... (or slot, slot - 1, ... for len < 0).  Passed by value: 2 KB of launch arguments.
+struct SlotRun {
+  int tok, slot, pos, len;
+};
+constexpr int kMaxRuns = 128;
+struct SlotRuns {
+  int n;
+  SlotRun r[kMaxRuns];
+};
+hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
+                                    int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
+hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
 int paged_units(int S, int Hkv, int max_blocks, int BS, int D);
 size_t paged_ws_bytes(int S, int Hq, int D, int units);
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,

@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cstdlib>
 
 namespace kvs {
 
@@ -55,6 +56,41 @@ __global__ void __launch_bounds__(256) paged_evict_kernel(const int* __restrict_
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const int slot = slots[i];
     if ((unsigned)slot < (unsigned)num_slots) slot_pos[slot] = -1;
+  }
+}
+
+// The same from slot lists the host holds, run by run: the slots a block manager
+// hands out lie in a few runs (a block's rows, and often blocks in a row), which
+// fit the launch's arguments, so nothing is uploaded.  blockIdx.y is the run.
+// Token i of a run: slot + i * step, position + i.
+template <int D>
+__global__ void __launch_bounds__(256) paged_append_runs_kernel(const uint16_t* __restrict__ kn,
+                                                                const uint16_t* __restrict__ vn, SlotRuns runs,
+                                                                uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
+                                                                int* __restrict__ slot_pos, int num_slots, int Hkv,
+                                                                int BS) {
+  const SlotRun run = runs.r[blockIdx.y];
+  const long long per_tok = (long long)Hkv * (D / 8), chunks = (long long)(run.len < 0 ? -run.len : run.len) * per_tok;
+  for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < chunks;
+       c += (long long)gridDim.x * blockDim.x) {
+    const long long i = c / per_tok, r = c - i * per_tok, src = ((long long)run.tok + i) * per_tok + r;
+    const long long slot = run.slot + (run.len < 0 ? -i : i);
+    if (slot < 0 || slot >= num_slots) continue;
+    const int h = (int)(r / (D / 8)), d8 = (int)(r - (long long)h * (D / 8));
+    const long long dst = (((slot / BS) * Hkv + h) * BS + slot % BS) * D + 8 * d8;
+    *reinterpret_cast<uint4*>(kc + dst) = *reinterpret_cast<const uint4*>(kn + src * 8);
+    *reinterpret_cast<uint4*>(vc + dst) = *reinterpret_cast<const uint4*>(vn + src * 8);
+    if (r == 0) slot_pos[slot] = (int)(run.pos + i);
+  }
+}
+
+__global__ void __launch_bounds__(256) paged_evict_runs_kernel(SlotRuns runs, int* __restrict__ slot_pos,
+                                                               int num_slots) {
+  const SlotRun run = runs.r[blockIdx.y];
+  const int n = run.len < 0 ? -run.len : run.len;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const long long slot = (long long)run.slot + (run.len < 0 ? -i : i);
+    if (slot >= 0 && slot < num_slots) slot_pos[slot] = -1;
   }
 }
 
@@ -497,6 +533,10 @@ template __global__ void paged_append_kernel<64>(const uint16_t*, const uint16_t
                                                  uint16_t*, uint16_t*, int*, int, int, int);
 template __global__ void paged_append_kernel<128>(const uint16_t*, const uint16_t*, const int*, const int*, int,
                                                   uint16_t*, uint16_t*, int*, int, int, int);
+template __global__ void paged_append_runs_kernel<64>(const uint16_t*, const uint16_t*, SlotRuns, uint16_t*, uint16_t*,
+                                                      int*, int, int, int);
+template __global__ void paged_append_runs_kernel<128>(const uint16_t*, const uint16_t*, SlotRuns, uint16_t*,
+                                                       uint16_t*, int*, int, int, int);
 template __global__ void paged_decode_kernel<64>(DecodeArgs);
 template __global__ void paged_decode_kernel<128>(DecodeArgs);
 template __global__ void paged_combine_kernel<64, 1>(DecodeArgs);
@@ -507,6 +547,29 @@ template __global__ void paged_combine_kernel<128, 4>(DecodeArgs);
 template __global__ void paged_combine_kernel<128, 16>(DecodeArgs);
 
 // ---------------------------------------------------------------- launchers
+hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
+                                    int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream) {
+  int longest = 1;
+  for (int i = 0; i < runs.n; ++i) longest = std::max(longest, std::abs(runs.r[i].len));
+  const long long chunks = (long long)longest * Hkv * (D / 8);
+  const dim3 grid((unsigned)std::min<long long>((chunks + 255) / 256, 4096), (unsigned)runs.n);
+  if (D == 128)
+    hipLaunchKernelGGL(paged_append_runs_kernel<128>, grid, dim3(256), 0, stream, (const uint16_t*)kn,
+                       (const uint16_t*)vn, runs, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
+  else
+    hipLaunchKernelGGL(paged_append_runs_kernel<64>, grid, dim3(256), 0, stream, (const uint16_t*)kn,
+                       (const uint16_t*)vn, runs, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
+  return hipGetLastError();
+}
+
+hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream) {
+  int longest = 1;
+  for (int i = 0; i < runs.n; ++i) longest = std::max(longest, std::abs(runs.r[i].len));
+  const dim3 grid((unsigned)std::min((longest + 255) / 256, 4096), (unsigned)runs.n);
+  hipLaunchKernelGGL(paged_evict_runs_kernel, grid, dim3(256), 0, stream, runs, slot_pos, num_slots);
+  return hipGetLastError();
+}
+
 // Units of the decode grid per KV head: one round of the resident waves (D =
 // 128: four per CU, D = 64: eight), and for more sequences than that half a
 // round on top of one unit each, so that long sequences of a ragged batch can

@@ -61,6 +61,8 @@ SIGNATURES = {
     "kvs_bm_live": (_I, [_P, _I]),
     "kvs_paged_append": (_I, [_P, _P, _P, _P, _I, _P, _P, _P, _I, _I, _I, _I, _P]),
     "kvs_paged_evict": (_I, [_P, _I, _P, _I, _I, _P]),
+    "kvs_paged_append_host": (_I, [_P, _P, _P, _P, _I, _P, _P, _P, _I, _I, _I, _I, _P]),
+    "kvs_paged_evict_host": (_I, [_P, _I, _P, _I, _I, _P]),
     "kvs_paged_decode_workspace": (_Z, [_I, _I, _I, _I, _I, _I]),
     "kvs_paged_decode": (_I, [_P, _P, _P, _P, _P, _P, _P, _P, _I, _I, _I, _I, _I, _I, _I, _F, _P, _Z, _P]),
 }

@@ -17,7 +17,7 @@ from typing import Optional, Sequence, Tuple
 import numpy as np
 import torch
 
-from .kvs import KvsError, _check, _ptr, _stream, _workspace, lib
+from .kvs import KVS_ERR_UNSUPPORTED, KvsError, _check, _ptr, _stream, _workspace, lib
 
 
 def _i32(a) -> np.ndarray:
@@ -25,7 +25,7 @@ def _i32(a) -> np.ndarray:
 
 
 def _np_ptr(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.c_void_p)
+    return a.__array_interface__["data"][0]
 
 
 class BlockManager:
@@ -141,29 +141,50 @@ class PagedKVCache:
             raise ValueError("k_new/v_new must be [n, Hkv, D]")
         slots = self.bm.append(seq, pos)
         if pos.size:
-            kvs_paged_append(k_new.contiguous(), v_new.contiguous(), torch.from_numpy(pos).to(self.device),
-                             torch.from_numpy(slots).to(self.device), self.k, self.v, self.slot_pos, self.block_size)
+            k_new, v_new = k_new.contiguous(), v_new.contiguous()
+            st = lib.kvs_paged_append_host(_ptr(k_new), _ptr(v_new), _np_ptr(pos), _np_ptr(slots), pos.size,
+                                           _ptr(self.k), _ptr(self.v), _ptr(self.slot_pos), self.num_blocks,
+                                           self.block_size, self.Hkv, self.D, _stream(self.k))
+            if st == KVS_ERR_UNSUPPORTED:   # too many runs of slots for the launch's arguments
+                kvs_paged_append(k_new, v_new, torch.from_numpy(pos).to(self.device),
+                                 torch.from_numpy(slots).to(self.device), self.k, self.v, self.slot_pos,
+                                 self.block_size)
+            else:
+                _check("kvs_paged_append_host", st)
         self._tables = None
         return slots
+
+    def _mark_evicted(self, slots: np.ndarray) -> None:
+        st = lib.kvs_paged_evict_host(_np_ptr(slots), slots.size, _ptr(self.slot_pos), self.num_blocks,
+                                      self.block_size, _stream(self.slot_pos))
+        if st == KVS_ERR_UNSUPPORTED:
+            kvs_paged_evict(torch.from_numpy(slots).to(self.device), self.slot_pos, self.num_blocks, self.block_size)
+        else:
+            _check("kvs_paged_evict_host", st)
 
     def evict(self, seq: int, positions) -> np.ndarray:
         slots = self.bm.evict(seq, _i32(positions))
         if slots.size:
-            kvs_paged_evict(torch.from_numpy(slots).to(self.device), self.slot_pos, self.num_blocks, self.block_size)
+            self._mark_evicted(slots)
         self._tables = None
         return slots
 
     def release(self, seq: int) -> np.ndarray:
         slots = self.bm.release(seq)
         if slots.size:
-            kvs_paged_evict(torch.from_numpy(slots).to(self.device), self.slot_pos, self.num_blocks, self.block_size)
+            self._mark_evicted(slots)
         self._tables = None
         return slots
 
     def device_tables(self) -> Tuple[torch.Tensor, torch.Tensor]:
         if self._tables is None:
-            table, nblk = self.bm.tables()
-            self._tables = (torch.from_numpy(table).to(self.device), torch.from_numpy(nblk).to(self.device))
+            # both tables in one upload: the block counts behind the block lists
+            n = self.num_seqs * self.max_blocks
+            both = np.empty(n + self.num_seqs, dtype=np.int32)
+            p = _np_ptr(both)
+            _check("kvs_bm_tables", lib.kvs_bm_tables(self.bm._h, p, p + 4 * n))
+            dev = torch.from_numpy(both).to(self.device)
+            self._tables = (dev[:n].view(self.num_seqs, self.max_blocks), dev[n:])
         return self._tables
 
     def decode(self, q: torch.Tensor, softmax_scale=None, out=None, lse=None):
