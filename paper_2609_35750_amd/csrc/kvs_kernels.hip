@@ -12,10 +12,10 @@
 // queries on N), so each lane holds 16 scores of a single query and the row
 // max / row sum need one cross-lane exchange per tile.
 //
-// Column kernel (dK, dV): a workgroup owns 128 keys of one KV head (32 per
-// wave, with K and V held in registers) and walks the contiguous range of
-// query rows that can see any of them, for each q-head of the group; Q, dO,
-// LSE and Delta blocks of 32 rows are staged in LDS.
+// Column kernel (dK, dV): a workgroup owns 128 keys of one KV head (K held in
+// registers, V in LDS) and walks the contiguous range of query rows that can
+// see any of them, for each q-head of the group, in steps of 64 rows whose Q,
+// dO, LSE and Delta are staged in LDS; a wave takes 32 keys x 32 rows of a step.
 //
 // All MFMAs are v_mfma_f32_32x32x16_bf16 (bf16 in, fp32 accumulate).
 // Operand layouts (per lane l, h = l / 32):  A[m = l%32][k = 8h .. 8h+7],
@@ -679,43 +679,46 @@ __global__ void __launch_bounds__(512) dq_kernel(RowArgs a) {
 }
 
 // ---------------------------------------------------------------- backward: dK, dV (column kernel)
-// One workgroup: 128 keys of one KV head, 8 waves.  Wave w < 4 (the "dV
-// wave") and wave w + 4 (the "dK wave") own the same 32 keys and share a SIMD.
-// The workgroup walks the query rows that can see any of its keys in steps of
-// 64 rows x one q-head of the group; Q, dO, LSE and Delta of a step are staged
-// once in LDS for all eight waves.  Per 32-row block:
-//   dV wave:  S = Q K^T,  P = exp2(S * scale * log2 e - LSE * log2 e) (masked),
-//             P -> LDS (bf16),  dV^T += dO^T P
-//   dK wave:  dP = dO V^T - Delta,  dS = P dP  (P read back from LDS),
-//             dK^T += Q^T dS
-// The dV waves run one step ahead of the dK waves (P of step s is written
-// during step s - 1), so a single barrier per step orders the exchange, every
-// product is computed once, and the two waves of a SIMD issue the same number
-// of MFMAs.  Masking happens only in the dV wave (masked P = 0 gives dS = 0).
+// One workgroup: 128 keys of one KV head, 8 waves.  The workgroup walks the
+// query rows that can see any of its keys in steps of 64 rows x one q-head of
+// the group; Q, dO, LSE and Delta of a step are staged once in LDS for all
+// eight waves.  Wave w computes the 32 keys 32 (w % 4) .. and the 32-row block
+// w / 4 of every step, all of it by itself:
+//   S = Q K^T,  P = exp2(S * scale * log2 e - LSE * log2 e) (masked),  dV^T += dO^T P,
+//   dP = dO V^T - Delta,  dS = P dP,  dK^T += Q^T dS
+// so the waves of a SIMD (w and w + 4) exchange nothing inside an item and P
+// stays in registers.  K is held in registers; V, which does not fit beside the
+// dK and dV accumulators (2 x 64 registers at D = 128 of a wave's 256), is
+// staged in LDS once per item.  At the item's end the two row halves are added
+// through the (then free) tile buffers: wave w < 4 stores dV, wave w + 4 dK.
+// Bound by the matrix cores (62% busy on the 16k trace) at the clock their power
+// leaves: each wave is one chain of S, dP, the exponentials, dV and dK, and two
+// waves a SIMD cover each other's.  A pair of waves that splits the products
+// instead (one S and dV, the other dP and dK of the same block, P through LDS in
+// 16 bits) is locked together by every step's barrier: 15% more cycles, 53% busy,
+// at a clock 8% higher.  That against this, us: 16k trace (32/8 heads, D = 128)
+// 1,994 -> 1,812, two of 4,097 406 -> 357, 24 of 100 to 1,500 (16/2) 138 -> 127,
+// 8,191 tokens (24/8, D = 64) 229 -> 207, 512 tokens (4/4, D = 64) 14.7 -> 14.0.
 template <int D>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) dkdv_kernel(ColArgs a) {
-  constexpr int KS = D / 16, DB = D / 32, PITCH = Lay<D>::PITCH;
-  __shared__ __attribute__((aligned(1024))) uint16_t sQ0[kQStep * PITCH];
-  __shared__ __attribute__((aligned(1024))) uint16_t sQ1[kQStep * PITCH];
-  __shared__ __attribute__((aligned(1024))) uint16_t sQ2[kQStep * PITCH];
-  __shared__ __attribute__((aligned(1024))) uint16_t sO0[kQStep * PITCH];
-  __shared__ __attribute__((aligned(1024))) uint16_t sO1[kQStep * PITCH];
-  __shared__ __attribute__((aligned(1024))) uint16_t sO2[kQStep * PITCH];
-  __shared__ __attribute__((aligned(256))) float sL0[kQStep];
-  __shared__ __attribute__((aligned(256))) float sL1[kQStep];
-  __shared__ __attribute__((aligned(256))) float sL2[kQStep];
-  __shared__ __attribute__((aligned(256))) float sD0[kQStep];
-  __shared__ __attribute__((aligned(256))) float sD1[kQStep];
-  __shared__ __attribute__((aligned(256))) float sD2[kQStep];
-  // P exchange: [step parity][key quarter][32-row block][half of the 16 values][lane], 8 fp16 each
-  // (P <= 1; fp16 keeps 3 more mantissa bits than bf16 for dS = P dP)
-  __shared__ __attribute__((aligned(1024))) f16x8 sP[2 * 4 * 2 * 2 * kWave];
+  constexpr int KS = D / 16, DB = D / 32, PITCH = Lay<D>::PITCH, kHalf = kQStep * PITCH, kTile = 2 * kHalf;
+  using LV = Lay<D, true>;
+  constexpr int AHEAD = 2, OPS = 2;
+  // ring of three tiles: [Q rows, dO rows], and their [LSE * log2 e, -Delta].  One array each, indexed by the
+  // step: with an array a tile, every tile's operand addresses would be held in registers (24 of them spilled).
+  __shared__ __attribute__((aligned(1024))) uint16_t sT[3 * kTile];
+  __shared__ __attribute__((aligned(1024))) uint16_t sV[kColKeys * LV::PITCH];
+  __shared__ __attribute__((aligned(256))) float sW[3 * 2 * kQStep];
   __shared__ int sEmax[4];
   __shared__ int sNext;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool role_dk = wave >= 4;
-  const int kw = wave & 3;
+  const bool role_dk = wave >= 4;       // what the wave stores at the item's end
+  const int kw = wave & 3;              // its keys
+  const int rb = 32 * (wave >> 2);      // its rows of a step
+  // The second wave of a SIMD gets its copies out last; with priority it catches up with the first one's products
+  // instead of ending every step behind it (16k trace, backward: 2,975 -> 2,950 us, with the early reads below).
+  if (role_dk) __builtin_amdgcn_s_setprio(1);
 
   // Work items (longest first, see split_plan_kernel): a whole key block, or
   // one part of a split block; one KV head each.  The grid is one workgroup a
@@ -743,7 +746,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   asm volatile("" : "+v"(lane));
   const int half = lane >> 5, col = lane & 31;
   const auto rl = Lay<D>::row_lane(lane);
+  const int vl = LV::row_lane(lane).even + 32 * kw * LV::PITCH;
   const int tl = Lay<D>::tr_lo(lane), th = Lay<D>::tr_hi(lane);
+  {
+    // V of the block's keys (rows past the trace's end repeat its last 16 bytes and are masked)
+    RowStager<D, kColKeys, 8, true> vst;
+    vst.init(wave, lane, (long long)a.Hkv * D);
+    vst.issue(lds_addr(sV), a.v + ((size_t)tr.tok0 * a.Hkv + g) * D, (long long)a.Hkv * D, j0, tr.L - 1, wave);
+  }
   RowStager<D, kQStep, 8> qst;
   qst.init(wave, lane, (long long)a.Hq * D);
   const int j = j0 + 32 * kw + col;
@@ -757,15 +767,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     emin_w = min(emin_w, __shfl_xor(emin_w, off));
     emax_w = max(emax_w, __shfl_xor(emax_w, off));
   }
+  emin_w = __builtin_amdgcn_readfirstlane(emin_w);
+  emax_w = __builtin_amdgcn_readfirstlane(emax_w);
   if (!role_dk && lane == 0) sEmax[kw] = emax_w;
 
-  // K (dV waves) or V (dK waves) of this lane's key: the B operand of S or dP
-  bf16x8 kvreg[KS];
+  // K of this lane's key: the B operand of S
+  bf16x8 kreg[KS];
   {
-    const size_t koff = ((size_t)(tr.tok0 + jc) * a.Hkv + g) * D + 8 * half;
-    const uint16_t* src = role_dk ? a.v : a.k;
+    const uint16_t* src = a.k + ((size_t)(tr.tok0 + jc) * a.Hkv + g) * D + 8 * half;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kvreg[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(src + koff + 16 * ks));
+    for (int ks = 0; ks < KS; ++ks) kreg[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(src + 16 * ks));
   }
   __syncthreads();
   const int emax_wg = max(max(sEmax[0], sEmax[1]), max(sEmax[2], sEmax[3]));
@@ -778,9 +789,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     steps = min(per, steps - step0);
   }
 
-  f32x16 acc[DB];   // dV^T (dV waves) or dK^T (dK waves): rows d, column = this lane's key
+  f32x16 av[DB], ak[DB];   // dV^T and dK^T of the wave's rows: rows d, column = this lane's key
 #pragma unroll
-  for (int d = 0; d < DB; ++d) acc[d] = f32x16{};
+  for (int d = 0; d < DB; ++d) av[d] = ak[d] = f32x16{};
 
   // First row of a step and the byte offsets of its first Q / dO row and its
   // first LSE / Delta value, advanced step by step: from the step number they
@@ -802,295 +813,178 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     return wrap;
   };
   const Pos first = {(qs_lo + step0 / a.G) * kQStep, step0 % a.G};
-  const Src src0 = {first, row_step * ((long long)(tr.tok0 + first.i0) * a.Hq + g * a.G + first.hh),
-                    4ll * lse_index(a.varlen, a.ntok, a.Hq, a.T, b, g * a.G + first.hh, tr.tok0, first.i0)};
-  auto stage = [&](uint16_t* q_, uint16_t* o_, float* l_, float* d_, Src& s) __attribute__((always_inline)) {
-    const int dr = tr.L - 1 - s.at.i0;
+  Src next = {first, row_step * ((long long)(tr.tok0 + first.i0) * a.Hq + g * a.G + first.hh),
+              4ll * lse_index(a.varlen, a.ntok, a.Hq, a.T, b, g * a.G + first.hh, tr.tok0, first.i0)};   // staged next
+  Pos cur = first;                                                                                       // computed next
+  const uint32_t tile_lds = lds_addr(sT), word_lds = lds_addr(sW);
+  auto stage = [&](int buf) __attribute__((always_inline)) {
+    const int dr = tr.L - 1 - next.at.i0;
     const uint32_t lim = qst.limit(dr, (long long)a.Hq * D);
-    qst.issue_at(lds_addr(q_), (const char*)a.q + s.row, lim, wave);
-    qst.issue_at(lds_addr(o_), (const char*)a.dout + s.row, lim, wave);
-    if (wave == 6) stage_words_at(lds_addr(l_), (const char*)a.lse + s.word, dr, lane);   // LSE * log2(e)
-    if (wave == 7) stage_words_at(lds_addr(d_), (const char*)a.delta + s.word, dr, lane);
-    const bool wrap = advance(s.at);
-    s.row += row_step + (wrap ? row_wrap : 0);
-    s.word += word_step + (wrap ? word_wrap : 0);
+    qst.issue_at(tile_lds + 2 * buf * kTile, (const char*)a.q + next.row, lim, wave);
+    qst.issue_at(tile_lds + 2 * (buf * kTile + kHalf), (const char*)a.dout + next.row, lim, wave);
+    if (wave == 6) stage_words_at(word_lds + 8 * buf * kQStep, (const char*)a.lse + next.word, dr, lane);   // LSE * log2(e)
+    if (wave == 7) stage_words_at(word_lds + 8 * buf * kQStep + 4 * kQStep, (const char*)a.delta + next.word, dr, lane);
+    const bool wrap = advance(next.at);
+    next.row += row_step + (wrap ? row_wrap : 0);
+    next.word += word_step + (wrap ? word_wrap : 0);
   };
   const int jw0 = j0 + 32 * kw;
-  auto xslot = [&](int step, int blk, int t) __attribute__((always_inline)) { return sP + ((((step & 1) * 4 + kw) * 2 + blk) * 2 + t) * kWave + lane; };
 
-  // acc += (dO^T or Q^T) x for one 32-row block (A operand read transposed from the staged tile)
-  auto block_acc = [&](const uint16_t* src, int rb, const bf16x8 (&xb)[2]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) acc[d] = mfma32(tr_operand<D>(src, rb + 16 * t, 32 * d, tl, th), xb[t], acc[d]);
+  f32x16 dp;   // dP - Delta: the product starts at -Delta
+  bf16x8 qa[AHEAD], oa[AHEAD], va[AHEAD];
+  auto read_ks = [&](int buf, int ks) __attribute__((always_inline)) {
+    const uint16_t *cQ = sT + buf * kTile, *cO = cQ + kHalf;
+    qa[ks % AHEAD] = lds_read_b128(cQ + rb * PITCH + Lay<D>::row_at(rl, ks));
+    oa[ks % AHEAD] = lds_read_b128(cO + rb * PITCH + Lay<D>::row_at(rl, ks));
+    va[ks % AHEAD] = lds_read_b128(sV + LV::row_at({vl}, ks));
   };
-  // dV wave, one 32-row block: S = Q K^T (C layout: lane <-> key, element r <->
-  // row rb + 8 (r/4) + 4 half + r%4 of the staged tile), P, P -> LDS, dV^T += dO^T P.
-  auto dv_block_s = [&](const uint16_t* cQ, const float* cL, int rb, int ib, bool partial, bf16x8 (&pb)[2],
-                        f16x8 (&ph)[2]) __attribute__((always_inline)) {
-    f32x16 x = {};
+  // the first operands of a tile: read ahead of the barrier in front of its step (in registers the step before
+  // has done with), unused if the block turns out EMPTY
+  auto read_first = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) x = mfma32(lds_read_b128(cQ + rb * PITCH + Lay<D>::row_at(rl, ks)), kvreg[ks], x);
+    for (int ks = 0; ks < AHEAD; ++ks) read_ks(buf, ks);
+    const float* cD = sW + buf * 2 * kQStep + kQStep;
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      const float4 l4 = *reinterpret_cast<const float4*>(cL + rb + 8 * q4 + 4 * half);
-      const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
-#pragma unroll
-      for (int t = 0; t < 4; ++t) x[4 * q4 + t] = __builtin_fmaf(x[4 * q4 + t], a.scale_log2, -lv[t]);
+      const float4 d4 = *reinterpret_cast<const float4*>(cD + rb + 8 * q4 + 4 * half);
+      dp[4 * q4] = d4.x;
+      dp[4 * q4 + 1] = d4.y;
+      dp[4 * q4 + 2] = d4.z;
+      dp[4 * q4 + 3] = d4.w;
     }
-    if (partial) {
+  };
+  // The wave's block of a step.  C layout of S and dP: lane <-> key, element r
+  // <-> row rb + 8 (r/4) + 4 half + r%4 of the staged tile.  Operands are read
+  // AHEAD k-steps (S, dP) or OPS products (dV, dK) before their product, and the
+  // arithmetic of one group of products stands between the products of the
+  // group before it; fences keep the compiler from moving the reads back to
+  // their products (which waits out an LDS latency per product).
+  auto compute = [&](int buf) __attribute__((always_inline)) {
+    const int ib = cur.i0 + rb;
+    const int cls = adjust_class(tile_class(ib, ib + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
+    if (cls == kEmpty) return;
+    const uint16_t *cQ = sT + buf * kTile, *cO = cQ + kHalf;
+    const float* cL = sW + buf * 2 * kQStep;
+    f32x16 x = {};
+    float4 l4[4];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      x = mfma32(qa[ks % AHEAD], kreg[ks], x);
+      dp = mfma32(oa[ks % AHEAD], va[ks % AHEAD], dp);
+      if (ks + AHEAD < KS) read_ks(buf, ks + AHEAD);
+      if (ks + AHEAD == KS) {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) l4[q4] = *reinterpret_cast<const float4*>(cL + rb + 8 * q4 + 4 * half);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // operand n of dV (n < 2 DB) and dK
+    auto operand = [&](int n) __attribute__((always_inline)) {
+      return tr_operand<D>(n < 2 * DB ? cO : cQ, rb + 16 * ((n / DB) & 1), 32 * (n % DB), tl, th);
+    };
+    bf16x8 op[OPS + 1];
+#pragma unroll
+    for (int n = 0; n < OPS; ++n) op[n] = operand(n);
+    if (cls == kPartial) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const bool vis = (unsigned)(ib + 8 * (r >> 2) + 4 * half + (r & 3) - j) < kspan;
         x[r] = vis ? x[r] : -INFINITY;
       }
     }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = __builtin_amdgcn_exp2f(x[r]);
-    pb[0] = pack8(x, 0);
-    pb[1] = pack8(x, 8);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      ph[0][e] = (_Float16)x[e];
-      ph[1][e] = (_Float16)x[8 + e];
-    }
-  };
-  // dK wave, one 32-row block: dP = dO V^T - Delta, dS = P dP with P from LDS.
-  auto dk_block_s = [&](const uint16_t* cO, const float* cD, int rb, const f16x8* xp0, const f16x8* xp1,
-                        bf16x8 (&sb)[2]) __attribute__((always_inline)) {
-    f32x16 dp;
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const float4 d4 = *reinterpret_cast<const float4*>(cD + rb + 8 * q4 + 4 * half);
-      dp[4 * q4] = d4.x;   // -Delta
-      dp[4 * q4 + 1] = d4.y;
-      dp[4 * q4 + 2] = d4.z;
-      dp[4 * q4 + 3] = d4.w;
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) dp = mfma32(lds_read_b128(cO + rb * PITCH + Lay<D>::row_at(rl, ks)), kvreg[ks], dp);
-    const f16x8 p0 = *xp0, p1 = *xp1;
-    f32x16 x;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      x[e] = (float)p0[e] * dp[e];
-      x[8 + e] = (float)p1[e] * dp[8 + e];
-    }
-    sb[0] = pack8(x, 0);
-    sb[1] = pack8(x, 8);
-  };
-
-  // Both 32-row blocks FULL (the common case), written as one straight-line
-  // sequence whose order is pinned with scheduling fences: all LDS operands of
-  // the score products are requested before the first product, and the
-  // transposed operands of each accumulation are requested while the
-  // exponentials of that block are computed, so LDS latency overlaps work.
-  auto dv_full = [&](int step, const uint16_t* cQ, const uint16_t* cO, const float* cL) __attribute__((always_inline)) {
-    bf16x8 qa[2][KS];
-    float4 lv[2][4];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) qa[blk][ks] = lds_read_b128(cQ + 32 * blk * PITCH + Lay<D>::row_at(rl, ks));
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) lv[blk][q4] = *reinterpret_cast<const float4*>(cL + 32 * blk + 8 * q4 + 4 * half);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    f32x16 x[2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      x[blk] = f32x16{};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) x[blk] = mfma32(qa[blk][ks], kvreg[ks], x[blk]);
-    }
-    bf16x8 tA[2][DB], tB[2][DB];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) tA[t][d] = tr_operand<D>(cO, 16 * t, 32 * d, tl, th);
-    __builtin_amdgcn_sched_barrier(0);
-    bf16x8 pb[2][2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const float lq[4] = {lv[blk][q4].x, lv[blk][q4].y, lv[blk][q4].z, lv[blk][q4].w};
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          x[blk][4 * q4 + t] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[blk][4 * q4 + t], a.scale_log2, -lq[t]));
-      }
-      pb[blk][0] = pack8(x[blk], 0);
-      pb[blk][1] = pack8(x[blk], 8);
-      f16x8 h0, h1;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        h0[e] = (_Float16)x[blk][e];
-        h1[e] = (_Float16)x[blk][8 + e];
-      }
-      *xslot(step, blk, 0) = h0;
-      *xslot(step, blk, 1) = h1;
-      if (blk == 0) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int d = 0; d < DB; ++d) tB[t][d] = tr_operand<D>(cO, 32 + 16 * t, 32 * d, tl, th);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int d = 0; d < DB; ++d) acc[d] = mfma32(tA[t][d], pb[0][t], acc[d]);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) acc[d] = mfma32(tB[t][d], pb[1][t], acc[d]);
-  };
-  auto dk_full = [&](int step, const uint16_t* cQ, const uint16_t* cO, const float* cD) __attribute__((always_inline)) {
-    bf16x8 oa[2][KS];
-    f32x16 dp[2];
-    f16x8 pr[2][2];
-    float4 dv4[2][4];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) oa[blk][ks] = lds_read_b128(cO + 32 * blk * PITCH + Lay<D>::row_at(rl, ks));
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) dv4[blk][q4] = *reinterpret_cast<const float4*>(cD + 32 * blk + 8 * q4 + 4 * half);
-      pr[blk][0] = *xslot(step, blk, 0);
-      pr[blk][1] = *xslot(step, blk, 1);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {   // start at -Delta, so the product gives dP - Delta
-        dp[blk][4 * q4] = dv4[blk][q4].x;
-        dp[blk][4 * q4 + 1] = dv4[blk][q4].y;
-        dp[blk][4 * q4 + 2] = dv4[blk][q4].z;
-        dp[blk][4 * q4 + 3] = dv4[blk][q4].w;
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) dp[blk] = mfma32(oa[blk][ks], kvreg[ks], dp[blk]);
-    }
-    bf16x8 tA[2][DB], tB[2][DB];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) tA[t][d] = tr_operand<D>(cQ, 16 * t, 32 * d, tl, th);
-    __builtin_amdgcn_sched_barrier(0);
-    bf16x8 sb[2][2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      f32x16 x;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) x[r] = (float)pr[blk][r >> 3][r & 7] * dp[blk][r];
-      sb[blk][0] = pack8(x, 0);
-      sb[blk][1] = pack8(x, 8);
-      if (blk == 0) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int d = 0; d < DB; ++d) tB[t][d] = tr_operand<D>(cQ, 32 + 16 * t, 32 * d, tl, th);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int d = 0; d < DB; ++d) acc[d] = mfma32(tA[t][d], sb[0][t], acc[d]);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) acc[d] = mfma32(tB[t][d], sb[1][t], acc[d]);
-  };
-  auto dv_step = [&](int step, int i0, const uint16_t* cQ, const uint16_t* cO, const float* cL) __attribute__((always_inline)) {
-    const int c0 = adjust_class(tile_class(i0, i0 + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
-    const int c1 = adjust_class(tile_class(i0 + 32, i0 + 64, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
-    if (c0 == kFull && c1 == kFull) {
-      dv_full(step, cQ, cO, cL);
-    } else {
-      if (c0 != kEmpty) {
-        bf16x8 p0[2];
-        f16x8 h0[2];
-        dv_block_s(cQ, cL, 0, i0, c0 == kPartial, p0, h0);
-        *xslot(step, 0, 0) = h0[0];
-        *xslot(step, 0, 1) = h0[1];
-        block_acc(cO, 0, p0);
-      }
-      if (c1 != kEmpty) {
-        bf16x8 p1[2];
-        f16x8 h1[2];
-        dv_block_s(cQ, cL, 32, i0 + 32, c1 == kPartial, p1, h1);
-        *xslot(step, 1, 0) = h1[0];
-        *xslot(step, 1, 1) = h1[1];
-        block_acc(cO, 32, p1);
-      }
-    }
-  };
-  auto dk_step = [&](int step, int i0, const uint16_t* cQ, const uint16_t* cO, const float* cD) __attribute__((always_inline)) {
-    const int c0 = adjust_class(tile_class(i0, i0 + 32, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
-    const int c1 = adjust_class(tile_class(i0 + 32, i0 + 64, jw0, jw0 + 32, tr.L, emin_w, emax_w), a.flags);
-    if (c0 != kEmpty && c1 != kEmpty) {
-      dk_full(step, cQ, cO, cD);
-    } else {
-      if (c0 != kEmpty) {
-        bf16x8 s0[2];
-        dk_block_s(cO, cD, 0, xslot(step, 0, 0), xslot(step, 0, 1), s0);
-        block_acc(cQ, 0, s0);
-      }
-      if (c1 != kEmpty) {
-        bf16x8 s1[2];
-        dk_block_s(cO, cD, 32, xslot(step, 1, 0), xslot(step, 1, 1), s1);
-        block_acc(cQ, 32, s1);
-      }
-    }
-  };
-
-  // Three-stage ring: during step s the dK waves read tile s, the dV waves tile
-  // s + 1, and tile s + 2 is copied into the buffer tile s - 1 used.
-  auto run = [&](auto dk_tag) __attribute__((always_inline)) {
-    constexpr bool DK = decltype(dk_tag)::value;
-    int step = 0;
-    Src next = src0;   // the tile staged next
-    Pos cur = first;   // the tile this wave computes next
-    auto body = [&](const uint16_t* cQ, const uint16_t* cO, const float* cD, const uint16_t* nQ, const uint16_t* nO,
-                    const float* nL, uint16_t* zQ, uint16_t* zO, float* zL, float* zD) __attribute__((always_inline)) {
-      if (step + 2 < steps) stage(zQ, zO, zL, zD, next);
-      if (DK) dk_step(step, cur.i0, cQ, cO, cD);
-      else if (step + 1 < steps) dv_step(step + 1, cur.i0, nQ, nO, nL);
-      advance(cur);
-      wait_vm();   // tile step + 2 has landed (the dV waves read it next step)
-      __syncthreads();
-      ++step;
+    auto prob = [&](int r) __attribute__((always_inline)) {
+      const float lv[4] = {l4[r >> 2].x, l4[r >> 2].y, l4[r >> 2].z, l4[r >> 2].w};
+      x[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], a.scale_log2, -lv[r & 3]));
     };
-    if (steps > 0) stage(sQ0, sO0, sL0, sD0, next);
-    if (steps > 1) stage(sQ1, sO1, sL1, sD1, next);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) prob(r);
+    bf16x8 pk[2];   // P, then dS, of the rows of each half of the products
+    pk[0] = pack8(x, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int E = 8 / DB;   // elements a product's arithmetic takes
+#pragma unroll
+    for (int n = 0; n < 4 * DB; ++n) {
+      f32x16& acc = n < 2 * DB ? av[n % DB] : ak[n % DB];
+      acc = mfma32(op[n % (OPS + 1)], pk[(n / DB) & 1], acc);
+      if (n + OPS < 4 * DB) op[(n + OPS) % (OPS + 1)] = operand(n + OPS);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int r = E * (n % DB) + e;
+        if (n < DB) prob(8 + r);
+        else if (n < 2 * DB) x[r] *= dp[r];
+        else if (n < 3 * DB) x[8 + r] *= dp[8 + r];
+      }
+      if (n == DB - 1) pk[1] = pack8(x, 8);
+      if (n == 2 * DB - 1) pk[0] = pack8(x, 0);
+      if (n == 3 * DB - 1) pk[1] = pack8(x, 8);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // Three-stage ring: during step s tile s is read and tile s + 2 copied into
+  // the buffer tile s - 1 used.  Every wave waits for its copies of tile s + 2
+  // ahead of the barrier that ends step s, so tile s + 1 is whole all through
+  // step s and its first operands may be read before that barrier.  The barrier
+  // itself only orders the copies behind the reads of step s, whose values the
+  // products have taken by then: no wait for LDS stands in front of it.
+  {
+    if (steps > 0) stage(0);
+    if (steps > 1) stage(1);
     wait_vm();
     __syncthreads();
-    if (!DK && steps > 0) {
-      dv_step(0, cur.i0, sQ0, sO0, sL0);
+    int buf = 0;
+    read_first(0);
+    for (int step = 0; step < steps; ++step) {
+      const int nbuf = buf == 2 ? 0 : buf + 1;
+      if (step + 2 < steps) stage(buf == 0 ? 2 : buf - 1);
+      compute(buf);
       advance(cur);
+      read_first(nbuf);
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      buf = nbuf;
     }
-    __syncthreads();
-    while (step < steps) {
-      body(sQ0, sO0, sD0, sQ1, sO1, sL1, sQ2, sO2, sL2, sD2);
-      if (step >= steps) break;
-      body(sQ1, sO1, sD1, sQ2, sO2, sL2, sQ0, sO0, sL0, sD0);
-      if (step >= steps) break;
-      body(sQ2, sO2, sD2, sQ0, sO0, sL0, sQ1, sO1, sL1, sD1);
-    }
-  };
-  if (role_dk) run(std::true_type{});
-  else run(std::false_type{});
+  }
 
-  int next = nidx;   // asked for ahead of the stores, waited for behind them
-  if (threadIdx.x == 0 && more) next = atomicAdd(&ctl->next[queue], 1);
+  int next_idx = nidx;   // asked for ahead of the stores, waited for behind them
+  if (threadIdx.x == 0 && more) next_idx = atomicAdd(&ctl->next[queue], 1);
+  // The row halves' sums: each wave hands the partner (w ^ 4) the accumulators
+  // it does not store, through its own buffer among the tiles', which are free.
+  auto buffer = [&](int w) { return w < 6 ? sT + w * kHalf : sV + (w - 6) * 64 * LV::PITCH; };
+  uint16_t *buf = buffer(wave), *other = buffer(wave ^ 4);
+  {
+    float* give = reinterpret_cast<float*>(buf) + 4 * lane;
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x16& x = role_dk ? av[d] : ak[d];
+        *reinterpret_cast<float4*>(give + (4 * d + q4) * 4 * kWave) =
+            make_float4(x[4 * q4], x[4 * q4 + 1], x[4 * q4 + 2], x[4 * q4 + 3]);
+      }
+  }
+  __syncthreads();
+  f32x16 acc[DB];
+  {
+    const float* take = reinterpret_cast<const float*>(other) + 4 * lane;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[d][r] = role_dk ? ak[d][r] : av[d][r];
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const float4 v = *reinterpret_cast<const float4*>(take + (4 * d + q4) * 4 * kWave);
+        acc[d][4 * q4] += v.x;
+        acc[d][4 * q4 + 1] += v.y;
+        acc[d][4 * q4 + 2] += v.z;
+        acc[d][4 * q4 + 3] += v.w;
+      }
+    }
+  }
   if (nchunk > 1) {
     // fp32 partial sums of this part: [slot][dV, dK][32-key group], each group
     // as the accumulators lie, [d][q4][lane][4], so that a store instruction
@@ -1103,16 +997,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         *reinterpret_cast<float4*>(dst + (4 * d + q4) * 4 * kWave) =
             make_float4(acc[d][4 * q4], acc[d][4 * q4 + 1], acc[d][4 * q4 + 2], acc[d][4 * q4 + 3]);
   } else {
-    // whole rows through LDS: every wave has its own buffer among the tiles', which are free
-    uint16_t* const bufs[8] = {sQ0, sQ1, sQ2, sO0, sO1, sO2, (uint16_t*)sP, (uint16_t*)(sP + 4 * 2 * 2 * kWave)};
-    uint16_t* buf = bufs[0];
-#pragma unroll
-    for (int w = 1; w < 8; ++w) buf = wave == w ? bufs[w] : buf;
-    store_rows<D>(acc, role_dk ? a.scale : 1.f, buf,
+    // whole rows through LDS, in the buffer this wave has just read (its own is still the partner's to read)
+    asm volatile("" ::: "memory");
+    store_rows<D>(acc, role_dk ? a.scale : 1.f, other,
                   (role_dk ? a.dk : a.dv) + ((size_t)(tr.tok0 + jw0) * a.Hkv + g) * D, (long long)a.Hkv * D, tr.L - jw0,
                   lane);
   }
-  if (threadIdx.x == 0) sNext = next;
+  if (threadIdx.x == 0) sNext = next_idx;
   __syncthreads();   // sNext; and every wave is done with the LDS of this item
   idx = __builtin_amdgcn_readfirstlane(sNext);
   }
