@@ -17,9 +17,11 @@ number formats instead of guessing it:
 * backward preprocess: ``Delta = sum(O_bf16 * dO)`` in fp32 and
   ``LSE * log2 e`` in fp32;
 * dK/dV kernel: ``P = exp2(S * scale * log2 e - LSE * log2 e)`` in fp32,
-  rounded to bf16 for ``dV += P^T dO`` and to fp16 for
-  ``dS = P (dP - Delta)`` (fp32 product, rounded to bf16), ``dK += dS^T Q``;
-  outputs ``bf16(dV)``, ``bf16(dK * scale)``;
+  rounded to bf16 for ``dV += P^T dO``; ``dS = P (dP - Delta)`` (fp32 product,
+  rounded to bf16), ``dK += dS^T Q``; outputs ``bf16(dV)``, ``bf16(dK * scale)``.
+  The model rounds this second P to fp16, as a kernel that passes it through
+  LDS does; the kernel multiplies by the fp32 P, so the modelled dK error bounds
+  its own from above;
 * dQ kernel: the same fp32 ``P`` unrounded, ``dS = bf16(P (dP - Delta))``,
   ``dQ = bf16((dS K) * scale)``.
 
