@@ -1025,7 +1025,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 // 1024 threads; block spans come from the 64-key tile statistics.
 // dK/dV time with parts of 64 row-steps only, cut beyond 128, and with these:
 // 24 traces of 100 to 1,500 tokens (16/2 heads, D = 128) 336 -> 141 us, two of
-// 4,097 (32/8) 450 -> 338 us, one of 8,191 (24/8, D = 64) 468 -> 198 us.  Parts
+// 4,097 (32/8) 450 -> 338 us, one of 8,191 (24/8, D = 64) 468 -> 198 us (with the
+// kernel's products split over pairs of waves; 127, 357 and 207 now).  Parts
 // of 1/2 and 1/4 share and a threshold of 2/3 or 4/5 share: within 5% of that.
 __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict__ kstats, const int* __restrict__ cu,
                                                           int B, int T, int ntok, int nkt, int G, int Hkv, int capE,
