@@ -387,6 +387,22 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
         mx = halves_max(mx) * a.scale_log2;
+        // P is taken against the tile's own maximum, not the running one: what bf16 makes of it (the largest is 1,
+        // exactly) then depends on the tile alone and not on how many tiles the unit has.
+        const float m_tile = mx == -INFINITY ? 0.f : mx;
+        float l_tile = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sc[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], a.scale_log2, -m_tile));
+          l_tile += sc[r];
+        }
+        f32x16 ot[DB] = {};
+#pragma unroll
+        for (int t2 = 0; t2 < 2; ++t2) {
+          const bf16x8 pb = pack8(sc, 8 * t2);
+#pragma unroll
+          for (int d = 0; d < DB; ++d) ot[d] = mfma32(tr_operand<D, true>(cV, 16 * t2, 32 * d, tl, th), pb, ot[d]);
+        }
         if (mx > m_run) {   // per column (lane)
           const float alpha = __builtin_amdgcn_exp2f(m_run - mx);   // 0 on the first live tile
           l_run *= alpha;
@@ -396,18 +412,12 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
             for (int r = 0; r < 16; ++r) acc[d][r] *= alpha;
           m_run = mx;
         }
-        const float m_use = m_run == -INFINITY ? 0.f : m_run;
+        const float beta = __builtin_amdgcn_exp2f(mx - (m_run == -INFINITY ? 0.f : m_run));
+        l_run = __builtin_fmaf(l_tile, beta, l_run);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sc[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], a.scale_log2, -m_use));
-          l_run += sc[r];
-        }
+        for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2) {
-          const bf16x8 pb = pack8(sc, 8 * t2);
-#pragma unroll
-          for (int d = 0; d < DB; ++d) acc[d] = mfma32(tr_operand<D, true>(cV, 16 * t2, 32 * d, tl, th), pb, acc[d]);
-        }
+          for (int r = 0; r < 16; ++r) acc[d][r] = __builtin_fmaf(ot[d][r], beta, acc[d][r]);
       }
     }
 #pragma unroll
