@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "kvs_cache.h"
+#include "kvs_decode_plan.h"
 #include "kvs_launch.h"
 
 namespace {

@@ -83,7 +83,6 @@ struct SlotRuns {
 hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
                                     int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
 hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
-int paged_units(int S, int Hkv, int max_blocks, int BS, int D);
 size_t paged_ws_bytes(int S, int Hq, int D, int units);
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,
                                void* vc, int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);

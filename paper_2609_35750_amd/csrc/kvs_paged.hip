@@ -19,6 +19,7 @@
 // evicted or past the sequence's last slot, runs the online softmax per
 // column and accumulates O^T += V^T P^T.  Partial (max, sum, O) of every split
 // go to the workspace; a combine kernel merges them into O and LSE.
+#include "kvs_decode_plan.h"
 #include "kvs_device.h"
 #include "kvs_launch.h"
 
@@ -105,14 +106,18 @@ struct DecodeArgs {
   // rows of the partials: units * Hq, sequence s from seq_units[s].x * Hq on as [q-head][its units]
   float* part;            // [rows][D]: unnormalised O of each split (relative to its max)
   float2* part_ml;        // [rows]: max (log2 units), sum
-  int2* seq_units;        // [S]: first unit and number of units of the sequence
+  int plan;               // DecodePlan: how a wave finds its unit
+  int2* seq_units;        // kByWave: [S], first unit and number of units of the sequence
+  int4* unit_seq;         // kListed: [units], sequence, its slots, its first unit, its units (0: no such unit)
+  int* cut;               // kListed: number of cut sequences, their first units
   uint16_t* o;            // [S][Hq][D]: written here for sequences of one unit, by the merge for the others
   float* lse;             // [S][Hq]
   int S, Hq, Hkv, G, max_blocks, BS, num_blocks, units;
   float scale_log2;       // softmax_scale * log2(e)
 };
 
-constexpr int kDecTile = 32;   // cache slots per tile
+// One unit a sequence; each wave plans by itself; looked up in unit_seq, which the plan kernel wrote.
+enum DecodePlan : int { kOneUnit = 0, kByWave = 1, kListed = 2 };
 
 // The 32-slot tile's K or V rows (D = 128: 18 x 16-byte slots per padded LDS
 // row, 9 pieces of 64 lanes; D = 64: 9 per row, 4.5 pieces -> 5 with a guard).
@@ -156,29 +161,19 @@ struct GatherStager {
   }
 };
 
-// The split of the decode's work.  A unit is a run of a sequence's 32-slot
-// tiles that one wave walks per KV head; every sequence gets at least one.
-// All sequences are cut with one size, the smallest C tiles for which the
-// units fit the grid (paged_units), so ragged sequences give equal waves and
-// a table wider than what it holds costs nothing.  Each wave finds its unit
-// by itself from seq_blocks (S <= kPlanSeqs: lanes hold the tile counts in
-// registers and C is searched by bisection; beyond, C = total / (units - S),
-// which always fits since sum ceil(t / C) <= total / C + S).
+// The split of the decode's work (kvs_decode_plan.h).  Each wave finds its unit
+// by itself from seq_blocks where that costs less than a plan of its own (up
+// to four sequences a lane, and few rounds of waves: see launch_paged_decode);
+// otherwise paged_plan_kernel lists the units once.  The lookup is one scalar
+// load, and the merge walks the cut sequences only.
 // Cutting every sequence into the same number of splits instead: 24 rollouts
 // of 200 to 9,000 entries (D = 64, 195 MB) 51.8 -> 39.9 us, 40 of 500 to 8,000
 // (D = 128, 674 MB) 162 -> 119 us, one of 16,000 beside 63 of 200 379 -> 28 us
-// (these with the streamed gather); the plan itself adds 1 to 2 us to a wave.
-constexpr int kPlanRegs = 4, kPlanSeqs = kPlanRegs * kWave;
-// Least tiles of a unit.  A lone wave takes about 2 us a tile (one memory
-// latency), so small batches want many short units until the merge's reads
-// outweigh it: one rollout of 4,096 entries took 14.0 us with 4, 11.6 with 2.
-constexpr int kMinTiles = 2;
-
+// (these with the streamed gather).
 struct DecodeUnit {
   int s, nslots, first, n, chunk;   // sequence, its slots, its first unit, its units, this one among them
 };
 
-constexpr int kTileCap = 1 << 22;   // tiles of one sequence the plan tells apart (134 M slots); exact in fp32
 // x / y for x >= 0, y >= 1: float quotient, corrected, where x is exact in fp32 (an integer division of the
 // compiler's is several times the dependent instructions, on every wave's way to its first load)
 __device__ __forceinline__ int quick_div(int x, int y) {
@@ -187,78 +182,150 @@ __device__ __forceinline__ int quick_div(int x, int y) {
   const int r = x - q * y;
   return q + (r >= y) - (r < 0);
 }
-// max(1, ceil(t / C)) for 0 <= t <= kTileCap, C >= 1, rcpC = 1 / C
-__device__ __forceinline__ int unit_count(int t, int C, float rcpC) {
-  int q = (int)((float)t * rcpC);
-  int r = t - q * C;
-  if (r < 0) --q, r += C;
-  if (r >= C) ++q, r -= C;
-  return max(1, q + (r > 0));
-}
+
+// slots of the blocks sequence s uses (clamped to the table width; some may be evicted)
+__device__ __forceinline__ int slots_of(const DecodeArgs& a, int s) { return min(max(a.nblk[s], 0), a.max_blocks) * a.BS; }
 
 // The unit and KV head of workgroup `wg`; s = -1 past the last one.  All lanes
 // of the wave take part.  A sequence's workgroups are consecutive, its units
 // fastest, then the KV heads.
 __device__ __forceinline__ DecodeUnit decode_unit(const DecodeArgs& a, int wg, int lane, int& g) {
-  // slots of the blocks in use (clamped to the table width; some may be evicted)
-  auto slots_of = [&](int s) __attribute__((always_inline)) {
-    return s < a.S ? min(max(a.nblk[s], 0), a.max_blocks) * a.BS : 0;
-  };
-  auto tiles_of = [&](int ns) __attribute__((always_inline)) {
-    return (int)min(((unsigned)ns + kDecTile - 1) / kDecTile, (unsigned)kTileCap);
-  };
   const int u = quick_div(wg, a.Hkv);
-  int t[kPlanRegs], C = INT_MAX / 2;
-  const int ns0 = slots_of(lane);
-  t[0] = tiles_of(ns0);
+  g = wg - u * a.Hkv;
+  if (a.plan == kOneUnit) return {u, slots_of(a, u), u, 1, 0};
+  int s = 0, ns = 0, first = 0, n = 0;
+  if (a.plan == kListed) {
+    const int4 m = a.unit_seq[__builtin_amdgcn_readfirstlane(u)];
+    s = m.x, ns = m.y, first = m.z, n = m.w;
+    if (n == 0) return {-1, 0, 0, 0, 0};
+  } else {
+    int sl[kPlanRegs];   // slots of sequences 64 k + lane; -1: none
 #pragma unroll
-  for (int k = 1; k < kPlanRegs; ++k) t[k] = k * kWave < a.S ? tiles_of(slots_of(k * kWave + lane)) : 0;
-  if (a.S <= kPlanSeqs) {
-    // total <= 2^30: fits
-    const int total = wave_last(wave_scan(t[0] + t[1] + t[2] + t[3]));
+    for (int k = 0; k < kPlanRegs; ++k) {
+      const int i = k * kWave + lane;
+      sl[k] = k * kWave < a.S ? slots_of(a, min(i, a.S - 1)) : -1;
+      if (i >= a.S) sl[k] = -1;
+    }
+    int sum = 0, top = 0;   // at most 2^28
+#pragma unroll
+    for (int k = 0; k < kPlanRegs; ++k) {
+      const int t = plan_tiles(max(sl[k], 0));
+      sum += t;
+      top = max(top, t);
+    }
+    const int total = wave_last(wave_scan(sum));
+    auto count = [&](int slots, int c, float rc) __attribute__((always_inline)) {
+      return slots < 0 ? 0 : unit_count(plan_tiles(slots), c, rc);
+    };
     auto units_at = [&](int c) __attribute__((always_inline)) {
       const float rc = __builtin_amdgcn_rcpf((float)c);
-      int n = 0;
+      int m = 0;
 #pragma unroll
       for (int k = 0; k < kPlanRegs; ++k)
-        if (k * kWave < a.S) n += k * kWave + lane < a.S ? unit_count(t[k], c, rc) : 0;
-      return wave_last(wave_scan(n));
+        if (k * kWave < a.S) m += count(sl[k], c, rc);
+      return wave_last(wave_scan(m));
     };
-    C = max(kMinTiles, quick_div(total - 1, a.units) + 1);   // ceil(total / units), 1 for 0
-    if (units_at(C) > a.units) {
-      int lo = C, hi = min(total, kTileCap);   // units_at(lo) > units >= S = units_at(hi)
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (units_at(mid) > a.units) lo = mid;
-        else hi = mid;
+    auto upper = [&]() __attribute__((always_inline)) {
+      return min(wave_max(top), quick_div(total, a.units - a.S) + 1);
+    };
+    const int C = unit_size(quick_div(max(total - 1, 0), a.units) + 1, a.units, 30, units_at, upper);
+    const float rc = __builtin_amdgcn_rcpf((float)C);
+    int base = 0, l = -1;
+#pragma unroll
+    for (int k = 0; k < kPlanRegs; ++k) {
+      if (k * kWave < a.S && l < 0) {
+        const int m = count(sl[k], C, rc), incl = wave_scan(m);
+        const unsigned long long hit = __ballot(u < base + incl);
+        if (hit != 0ull) {
+          l = __builtin_ctzll(hit);
+          s = k * kWave + l;
+          ns = __builtin_amdgcn_readlane(sl[k], l);
+          n = __builtin_amdgcn_readlane(m, l);
+          first = base + __builtin_amdgcn_readlane(incl, l) - n;
+        }
+        base += wave_last(incl);
       }
-      C = hi;
     }
-  } else if (a.units > a.S) {
-    long long total = 0;   // below 2^53
-    for (int s0 = 0; s0 < a.S; s0 += kWave) total += wave_last(wave_scan(tiles_of(slots_of(s0 + lane))));
-    C = max(kMinTiles, (int)fmin((double)total / (a.units - a.S) + 1.0, (double)(INT_MAX / 2)));
+    if (l < 0) return {-1, 0, 0, 0, 0};
   }
+  const int rem = wg - first * a.Hkv;
+  g = __builtin_amdgcn_readfirstlane(quick_div(rem, n));
+  return {s, ns, first, n, rem - g * n};
+}
+
+// The plan of all sequences in one workgroup: unit_seq and cut.
+__global__ void __launch_bounds__(1024) paged_plan_kernel(DecodeArgs a) {
+  constexpr int NW = 1024 / kWave, KEEP = 4;   // waves; sequences a thread keeps in registers
+  __shared__ long long wsum[NW];
+  __shared__ int wtop[NW], wcnt[2][NW], ncut;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto tiles = [&](int s) { return plan_tiles(slots_of(a, s)); };
+  int t[KEEP];
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) t[k] = k * 1024 + tid < a.S ? tiles(k * 1024 + tid) : 0;
+  if (tid == 0) ncut = 0;
+  long long sum = 0;
+  int top = 0;
+  auto take = [&](int x) {
+    sum += x;
+    top = max(top, x);
+  };
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) take(t[k]);
+  for (int s = KEEP * 1024 + tid; s < a.S; s += 1024) take(tiles(s));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  top = wave_max(top);
+  if (lane == 0) {
+    wsum[wave] = sum;
+    wtop[wave] = top;
+  }
+  __syncthreads();
+  long long total = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    total += wsum[w];
+    top = max(top, wtop[w]);
+  }
+  int turn = 0;   // of two sets of counts: a wave may be one count ahead of the slowest reader
+  auto units_at = [&](int c) {
+    const float rc = __builtin_amdgcn_rcpf((float)c);
+    int m = 0;
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) m += k * 1024 + tid < a.S ? unit_count(t[k], c, rc) : 0;
+    for (int s = KEEP * 1024 + tid; s < a.S; s += 1024) m += unit_count(tiles(s), c, rc);
+    m = wave_last(wave_scan(m));
+    turn ^= 1;
+    if (lane == 0) wcnt[turn][wave] = m;
+    __syncthreads();
+    m = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m += wcnt[turn][w];
+    return m;
+  };
+  auto upper = [&]() { return (int)min((long long)top, total / (a.units - a.S) + 1); };
+  const int C = unit_size((int)((max(total, 1ll) - 1) / a.units) + 1, a.units, 4, units_at, upper);
   const float rc = __builtin_amdgcn_rcpf((float)C);
   int base = 0;
-  for (int s0 = 0; s0 < a.S; s0 += kWave) {
-    const int ns = s0 == 0 ? ns0 : slots_of(s0 + lane);
-    const int n = s0 + lane < a.S ? unit_count(tiles_of(ns), C, rc) : 0;
-    const int incl = wave_scan(n);
-    const unsigned long long hit = __ballot(u < base + incl);
-    if (hit != 0ull) {
-      const int l = __builtin_ctzll(hit);
-      const int nl = __builtin_amdgcn_readlane(n, l);
-      const int first = base + __builtin_amdgcn_readlane(incl, l) - nl;
-      const int rem = wg - first * a.Hkv;
-      g = __builtin_amdgcn_readfirstlane(quick_div(rem, nl));
-      const int chunk = rem - g * nl;
-      return {s0 + l, __builtin_amdgcn_readlane(ns, l), first, nl, chunk};
+  for (int s0 = 0; s0 < a.S; s0 += 1024) {
+    const int s = s0 + tid, ns = s < a.S ? slots_of(a, s) : 0;
+    const int m = s < a.S ? unit_count(plan_tiles(ns), C, rc) : 0, incl = wave_scan(m);
+    turn ^= 1;
+    if (lane == kWave - 1) wcnt[turn][wave] = incl;
+    __syncthreads();
+    int first = base + incl - m;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int x = wcnt[turn][w];
+      first += w < wave ? x : 0;
+      base += x;
     }
-    base += wave_last(incl);
+    for (int i = 0; i < m; ++i) a.unit_seq[first + i] = make_int4(s, ns, first, m);
+    if (m > 1) a.cut[1 + atomicAdd(&ncut, 1)] = first;
   }
-  g = 0;
-  return {-1, 0, 0, 0, 0};
+  for (int u = base + tid; u < a.units; u += 1024) a.unit_seq[u] = make_int4(0, 0, 0, 0);
+  __syncthreads();
+  if (tid == 0) a.cut[0] = ncut;
 }
 
 // Copies in flight per wave: a ring of kDecRing tiles (K, V and the tile's
@@ -425,7 +492,7 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
     valid_q[R - 1] = 0u;
   }
 
-  if (lane == 0 && g == 0 && du.chunk == 0) a.seq_units[s] = make_int2(du.first, du.n);
+  if (a.plan == kByWave && lane == 0 && g == 0 && du.chunk == 0) a.seq_units[s] = make_int2(du.first, du.n);
   const float l_tot = halves_sum(l_run);
   if (!col_ok) return;
   if (du.n == 1) {   // the sequence's only unit: O and LSE directly
@@ -465,15 +532,13 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
 // about 4.5; 8.7 -> 4.5 us for 576 rows of 11 splits.
 constexpr int kMaxSplit = 2048;   // splits of one sequence: at most one round of resident waves, see paged_units
 template <int D, int W>
-__global__ void __launch_bounds__(64 * W) paged_combine_kernel(DecodeArgs a) {
+__device__ __forceinline__ void combine_row(const DecodeArgs& a, int r, int2 su) {
   constexpr int LPS = D / 4, P = kWave * W / LPS;   // lanes per split, splits per pass
   __shared__ float sw[kMaxSplit];
   __shared__ float sred[2][W];
   __shared__ float4 sx[kWave * W];
-  const int r = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
-  const int2 su = a.seq_units[r / a.Hq];
+  const int tid = threadIdx.x, wave = tid >> 6;
   const int nsplit = min(su.y, kMaxSplit);
-  if (nsplit <= 1) return;   // written by the decode itself
   const size_t row0 = (size_t)su.x * a.Hq + (size_t)(r % a.Hq) * su.y;   // split i is row row0 + i
   const float2* ml = a.part_ml + row0;
   const float4* pv = reinterpret_cast<const float4*>(a.part + row0 * D) + (tid & (LPS - 1));
@@ -525,18 +590,36 @@ __global__ void __launch_bounds__(64 * W) paged_combine_kernel(DecodeArgs a) {
   for (int i = tid / LPS + PRE * P; i < nsplit; i += P) add(pv[(size_t)i * LPS], sw[i]);
   sx[tid] = x;
   __syncthreads();
-  if (tid >= LPS) return;
+  if (tid < LPS) {
 #pragma unroll
-  for (int k = 1; k < P; ++k) {
-    const float4 v = sx[tid + k * LPS];
-    x.x += v.x;
-    x.y += v.y;
-    x.z += v.z;
-    x.w += v.w;
+    for (int k = 1; k < P; ++k) {
+      const float4 v = sx[tid + k * LPS];
+      x.x += v.x;
+      x.y += v.y;
+      x.z += v.z;
+      x.w += v.w;
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    reinterpret_cast<uint2*>(a.o + (size_t)r * D)[tid] = pack4_bf16(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+    if (tid == 0) a.lse[r] = L > 0.f ? (M + __log2f(L)) * 0.6931471805599453f : -INFINITY;
   }
-  const float inv = L > 0.f ? 1.f / L : 0.f;
-  reinterpret_cast<uint2*>(a.o + (size_t)r * D)[tid] = pack4_bf16(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
-  if (tid == 0) a.lse[r] = L > 0.f ? (M + __log2f(L)) * 0.6931471805599453f : -INFINITY;
+}
+
+// One row a workgroup (those of one split the decode has written itself), or, where they are listed, all rows of
+// the cut sequences.
+template <int D, int W, bool LISTED>
+__global__ void __launch_bounds__(64 * W) paged_combine_kernel(DecodeArgs a) {
+  if (!LISTED) {
+    const int2 su = a.seq_units[blockIdx.x / a.Hq];
+    if (su.y > 1) combine_row<D, W>(a, blockIdx.x, su);
+    return;
+  }
+  const int rows = a.cut[0] * a.Hq;
+  for (int i = blockIdx.x; i < rows; i += gridDim.x) {
+    const int4 m = a.unit_seq[a.cut[1 + i / a.Hq]];
+    combine_row<D, W>(a, m.x * a.Hq + i % a.Hq, make_int2(m.z, m.w));
+    __syncthreads();   // the next row's weights
+  }
 }
 
 template __global__ void paged_append_kernel<64>(const uint16_t*, const uint16_t*, const int*, const int*, int,
@@ -549,12 +632,14 @@ template __global__ void paged_append_runs_kernel<128>(const uint16_t*, const ui
                                                        uint16_t*, int*, int, int, int);
 template __global__ void paged_decode_kernel<64>(DecodeArgs);
 template __global__ void paged_decode_kernel<128>(DecodeArgs);
-template __global__ void paged_combine_kernel<64, 1>(DecodeArgs);
-template __global__ void paged_combine_kernel<64, 4>(DecodeArgs);
-template __global__ void paged_combine_kernel<64, 16>(DecodeArgs);
-template __global__ void paged_combine_kernel<128, 1>(DecodeArgs);
-template __global__ void paged_combine_kernel<128, 4>(DecodeArgs);
-template __global__ void paged_combine_kernel<128, 16>(DecodeArgs);
+template __global__ void paged_combine_kernel<64, 1, false>(DecodeArgs);
+template __global__ void paged_combine_kernel<64, 4, false>(DecodeArgs);
+template __global__ void paged_combine_kernel<64, 16, false>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 1, false>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 4, false>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 16, false>(DecodeArgs);
+template __global__ void paged_combine_kernel<64, 4, true>(DecodeArgs);
+template __global__ void paged_combine_kernel<128, 4, true>(DecodeArgs);
 
 // ---------------------------------------------------------------- launchers
 hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
@@ -580,21 +665,11 @@ hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_
   return hipGetLastError();
 }
 
-// Units of the decode grid per KV head: one round of the resident waves (D =
-// 128: four per CU, D = 64: eight), and for more sequences than that half a
-// round on top of one unit each, so that long sequences of a ragged batch can
-// still be cut; at most one unit per kMinTiles tiles of the table width.
-int paged_units(int S, int Hkv, int max_blocks, int BS, int D) {
-  const long long round = (D == 128 ? 4ll : 8ll) * 256;
-  const long long slack = (long long)S * Hkv <= (1 << 20) ? (round / 2 + Hkv - 1) / Hkv : 0;
-  const long long tiles = ((long long)max_blocks * BS + kDecTile - 1) / kDecTile;
-  const long long per_seq = (tiles + kMinTiles - 1) / kMinTiles;
-  return (int)std::min(std::max((round + Hkv - 1) / Hkv, S + slack), S * std::max(1ll, per_seq));
-}
 static size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 size_t paged_ws_bytes(int S, int Hq, int D, int units) {
   const size_t rows = (size_t)units * Hq;
-  return round256(rows * D * sizeof(float)) + round256(rows * sizeof(float2)) + round256((size_t)S * sizeof(int2));
+  return round256(rows * D * sizeof(float)) + round256(rows * sizeof(float2)) + round256((size_t)S * sizeof(int2)) +
+         round256((size_t)units * sizeof(int4));
 }
 
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,
@@ -621,23 +696,30 @@ hipError_t launch_paged_evict(const int* slots, int n, int* slot_pos, int num_sl
 // One wave a row while it covers the splits in four passes (8 splits at D = 128, 16 at D = 64): many rows
 // then, and one wave without a cross-wave exchange takes 4.9 us for 2,048 rows of two splits.  Beyond that
 // few rows with many splits each: four waves (11.3 -> 4.0 us for 256 rows of 16 splits), sixteen
-// beyond sixteen passes (9.8 -> 6.2 us for 32 rows of 128).
-static void launch_combine(int D, const DecodeArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)(a.S * a.Hq));
-  const int pass = D == 128 ? 2 : 4, avg = a.units / a.S;   // splits one wave reads at a time; units per sequence
-#define KVS_COMBINE(DD, WW) \
-  hipLaunchKernelGGL((paged_combine_kernel<DD, WW>), grid, dim3(kWave * WW), 0, stream, a)
-  if (D == 128) {
-    if (avg > 16 * pass) KVS_COMBINE(128, 16);
-    else if (avg > 4 * pass) KVS_COMBINE(128, 4);
-    else KVS_COMBINE(128, 1);
-  } else {
-    if (avg > 16 * pass) KVS_COMBINE(64, 16);
-    else if (avg > 4 * pass) KVS_COMBINE(64, 4);
-    else KVS_COMBINE(64, 1);
-  }
-#undef KVS_COMBINE
+// beyond sixteen passes (9.8 -> 6.2 us for 32 rows of 128).  These rows had equal splits: the width follows the
+// average, so that a lone long sequence of a ragged batch is merged by one wave (63 splits beside 63 sequences of
+// one).  Listed sequences are few and long: four waves.
+template <int W, bool LISTED>
+static void launch_combine(int D, int grid, const DecodeArgs& a, hipStream_t stream) {
+  if (D == 128) hipLaunchKernelGGL((paged_combine_kernel<128, W, LISTED>), dim3(grid), dim3(kWave * W), 0, stream, a);
+  else hipLaunchKernelGGL((paged_combine_kernel<64, W, LISTED>), dim3(grid), dim3(kWave * W), 0, stream, a);
 }
+static void launch_combine(int D, const DecodeArgs& a, hipStream_t stream) {
+  const int pass = D == 128 ? 2 : 4, avg = a.units / a.S;   // splits one wave reads at a time; units per sequence
+  if (a.plan == kListed)
+    launch_combine<4, true>(D, (int)std::min(std::min(a.S, a.units - a.S) * (long long)a.Hq, 2048ll), a, stream);
+  else if (avg > 16 * pass) launch_combine<16, false>(D, a.S * a.Hq, a, stream);
+  else if (avg > 4 * pass) launch_combine<4, false>(D, a.S * a.Hq, a, stream);
+  else launch_combine<1, false>(D, a.S * a.Hq, a, stream);
+}
+
+// Rounds of waves up to which each wave plans by itself (about 1 us a round, in every wave), beyond which a plan
+// kernel does (4 to 6 us, and a launch).  By wave against listed: 64 sequences of 200 entries (one round) 18.4 and
+// 22.0 us, 128 (1.5 rounds) 24.4 and 27.5, 256 (2.5 rounds) 45.3 and 46.4 (32/8 heads, D = 128).  More than kPlanSeqs
+// sequences were planned by wave too, at a cost that grows with their square: 2,048 of 200 347 us with no plan, 501
+// by wave, 294 now; 4,096 of 100 394, 1,050, 349; 1,024 of 300 under a wide table (8/2, D = 64) 31.7, 41.7, 35.9; one
+// of 16,000 beside 299 of 200 749, 78.5, 72.0.
+constexpr int kPlanRounds = 3;
 
 hipError_t launch_paged_decode(const PagedDecode& p) {
   DecodeArgs a{};
@@ -661,14 +743,19 @@ hipError_t launch_paged_decode(const PagedDecode& p) {
   a.part = (float*)p.ws;
   a.part_ml = (float2*)((char*)p.ws + round256(rows * p.D * sizeof(float)));
   a.seq_units = (int2*)((char*)a.part_ml + round256(rows * sizeof(float2)));
+  a.cut = (int*)a.seq_units;   // at most units - S cut sequences, and no more than S; S > 1 where they are listed
+  a.unit_seq = (int4*)((char*)a.seq_units + round256((size_t)p.S * sizeof(int2)));
   a.scale_log2 = p.scale * 1.4426950408889634f;
   const dim3 grid((unsigned)((long long)a.units * p.Hkv));
+  a.plan = a.units == p.S ? kOneUnit
+           : p.S <= kPlanSeqs && (long long)a.units * p.Hkv <= kPlanRounds * decode_round(p.D) ? kByWave : kListed;
+  if (a.plan == kListed) hipLaunchKernelGGL(paged_plan_kernel, dim3(1), dim3(1024), 0, p.stream, a);
   prof_begin("paged_decode", p.stream);
   if (p.D == 128) hipLaunchKernelGGL(paged_decode_kernel<128>, grid, dim3(64), 0, p.stream, a);
   else hipLaunchKernelGGL(paged_decode_kernel<64>, grid, dim3(64), 0, p.stream, a);
   prof_end(p.stream);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.plan == kOneUnit) return e;
   launch_combine(p.D, a, p.stream);
   return hipGetLastError();
 }

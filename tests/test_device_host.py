@@ -6,7 +6,8 @@ packed buffers and within max_seqlen; valid offsets pass unchanged) and the
 tile-classifier switches of the ``*_ex`` calls.  ``tests/host/stager_bounds.hip``
 checks the addressing of every staged tile: each LDS slot written once, every
 source read inside the trace's rows, and rows inside the trace copied
-unchanged through the swizzle."""
+unchanged through the swizzle.  ``tests/host/decode_plan.hip`` checks that the
+paged decode's units fit its grid and workspace."""
 import os
 import shutil
 import subprocess
@@ -39,4 +40,10 @@ def _build_and_run(tmp_path, src, name):
 @pytest.mark.skipif(HIPCC is None, reason="hipcc not available")
 def test_tile_copy_addressing(tmp_path):
     r = _build_and_run(tmp_path, "stager_bounds.hip", "stager_bounds")
+    assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr
+
+
+@pytest.mark.skipif(HIPCC is None, reason="hipcc not available")
+def test_decode_units_fit(tmp_path):
+    r = _build_and_run(tmp_path, "decode_plan.hip", "decode_plan")
     assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr

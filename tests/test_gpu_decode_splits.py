@@ -27,11 +27,25 @@ CASES = [
     ([4100, 129, 1, 0, 640, 127], 4, 5, 128, 5, 900),
     ([9001], 1, 8, 64, 1, 9100),             # one KV head: the most splits of a sequence
     ([300] * 70 + [2000, 0, 17], 8, 1, 128, 16, 130),   # more than 64 sequences
-    ([60 + 7 * i for i in range(140)], 8, 2, 64, 16, 70),   # more sequences than one round of waves holds
+    ([60 + 7 * i for i in range(140)], 8, 2, 64, 16, 70),   # more than 128 sequences: three registers a lane
+]
+
+# The same for batches whose units are listed by a plan kernel (more than 256
+# sequences, or more than three rounds of waves), and for those under a narrow
+# table, where every sequence is one unit.
+LISTED = [
+    ([40 + 9 * (i % 31) for i in range(257)], 2, 2, 64, 16, 70),
+    ([0, 3000] + [0, 17, 65, 33] * 63 + [1, 2500, 0], 8, 4, 128, 16, 190),
+    ([64 * (i % 3) for i in range(599)] + [5000], 8, 1, 64, 16, 320),
+    ([100] * 300 + [0] * 300, 4, 2, 128, 16, 300),     # equal ones and empty ones under a wide table
+    ([(7 * i) % 41 for i in range(5003)] + [2000], 1, 2, 64, 16, 126),   # more than the plan's threads hold
+    ([300, 0, 700] * 80, 16, 1, 128, 16, 200),         # 3,840 waves at 1,024 a round, fewer than 256 sequences
+    ([128, 0, 31] * 5, 3, 2, 64, 16, 8),               # one unit each: four tiles wide
+    ([(11 * i) % 513 for i in range(256)], 8, 2, 128, 16, 32),   # one unit each: 16 tiles, two rounds
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"S{len(c[0])}_max{max(c[0])}_Hkv{c[1]}_G{c[2]}_D{c[3]}_bs{c[4]}")
+@pytest.mark.parametrize("case", CASES + LISTED, ids=lambda c: f"S{len(c[0])}_max{max(c[0])}_Hkv{c[1]}_G{c[2]}_D{c[3]}_bs{c[4]}")
 def test_decode_split_shapes(case):
     from paper_2609_35750_amd import paged
 
