@@ -74,7 +74,7 @@ typedef enum {
   KVS_ERR_NULL = 1,         /* a required pointer is NULL */
   KVS_ERR_SHAPE = 2,        /* bad sizes: B,T,Hq,Hkv < 1, Hq % Hkv != 0, D not 64/128, bad BM/BN */
   KVS_ERR_ALIGN = 3,        /* a tensor pointer is not 16-byte aligned (workspace: 256-byte) */
-  KVS_ERR_WORKSPACE = 4,    /* workspace smaller than the *_workspace query */
+  KVS_ERR_WORKSPACE = 4,    /* workspace smaller than the call takes (the *_workspace query is always enough) */
   KVS_ERR_EVICT = 5,        /* invalid evict_at (only kvs_check_evict_at reports it) */
   KVS_ERR_HIP = 6,          /* a HIP launch or runtime call failed; see kvs_last_error() */
   KVS_ERR_UNSUPPORTED = 7,  /* valid but outside the supported limits above */
@@ -107,6 +107,13 @@ kvs_status_t kvs_evict_attn_fwd(const void* Q, const void* K, const void* V,
 /* ---------------------------------------------------------------- backward
  * Gradients of sum(dO * O) for the forward above: dQ, dK, dV (bf16, shapes
  * of Q, K, V).  O and LSE must be the forward's outputs for the same inputs.
+ * The query gives the size with which the dK/dV work of any batch is divided
+ * evenly over the GPU: most of it is fp32 partial sums, up to 1,024 (above
+ * 8,192 tokens 2,048) of 1 KB x D, so 128 MB from a few hundred tokens on at
+ * D = 128.  Traces of up to 8,192 tokens (max_seqlen) also run without any, with
+ * the statistics, two fp32 per (token, q-head) and 32 bytes per 128 keys, and
+ * with whatever lies in between: fewer or no key blocks are then cut, which
+ * changes the order of dK's and dV's sums and costs time.
  */
 size_t kvs_evict_attn_bwd_workspace(int B, int T, int Hq, int Hkv, int D);
 kvs_status_t kvs_evict_attn_bwd(const void* dO, const void* Q, const void* K, const void* V,

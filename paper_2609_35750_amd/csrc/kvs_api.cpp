@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -67,8 +68,16 @@ void head_grouping(kvs::Problem& p) {
 }
 
 size_t fwd_ws(int B, long long ntok) { return kvs::ws_kstats_bytes(B, (int)ntok); }
+size_t bwd_ws_fixed(int B, long long ntok, int Hq) {
+  return kvs::ws_kstats_bytes(B, (int)ntok) + kvs::ws_delta_bytes(Hq, (int)ntok);
+}
+// what the query gives, at least what a call takes
 size_t bwd_ws(int B, int T, long long ntok, int Hq, int Hkv, int D) {
-  return kvs::ws_kstats_bytes(B, (int)ntok) + kvs::ws_delta_bytes(Hq, (int)ntok) + kvs::ws_split_bytes(B, T, Hkv, Hq / Hkv, D);
+  return bwd_ws_fixed(B, ntok, Hq) +
+         std::max(kvs::ws_split_bytes(B, T, Hkv, Hq / Hkv, D), kvs::ws_split_least(B, T, Hkv, D));
+}
+size_t bwd_ws_least(int B, int T, long long ntok, int Hq, int Hkv, int D) {
+  return bwd_ws_fixed(B, ntok, Hq) + kvs::ws_split_least(B, T, Hkv, D);
 }
 
 kvs_status_t check_ws(void* ws, size_t have, size_t need) {
@@ -102,7 +111,7 @@ kvs_status_t run_bwd(kvs::Problem& p) {
   hipError_t e = kvs::launch_bwd_pre(p, kstats, delta);
   if (e != hipSuccess) return hip_fail(e, "backward preprocess launch");
   void* split_ws = (char*)delta + kvs::ws_delta_bytes(p.Hq, p.ntok);
-  e = kvs::launch_bwd_dkdv(p, kstats, delta, split_ws);
+  e = kvs::launch_bwd_dkdv(p, kstats, delta, split_ws, p.ws_bytes - bwd_ws_fixed(p.B, p.ntok, p.Hq));
   if (e != hipSuccess) return hip_fail(e, "dK/dV launch");
   e = kvs::launch_bwd_dq(p, kstats, delta);
   if (e != hipSuccess) return hip_fail(e, "dQ launch");
@@ -241,13 +250,13 @@ static kvs_status_t bwd_common(const void* dO, const void* Q, const void* K, con
   REQUIRE_PTR(dK, "dK");
   REQUIRE_PTR(dV, "dV");
   if (!evict_at) return fail(KVS_ERR_NULL, "evict_at is NULL");
-  st = check_ws(ws, ws_bytes, bwd_ws(B, T, ntok, Hq, Hkv, D));
+  st = check_ws(ws, ws_bytes, bwd_ws_least(B, T, ntok, Hq, Hkv, D));
   if (st != KVS_OK) return st;
   kvs::Problem p{};
   p.q = Q; p.k = K; p.v = V; p.o_in = O; p.dout = dO; p.lse_in = LSE; p.evict = evict_at; p.cu = cu;
   p.dq = dQ; p.dk = dK; p.dv = dV;
   p.B = B; p.T = T; p.ntok = (int)ntok; p.Hq = Hq; p.Hkv = Hkv; p.D = D; p.G = Hq / Hkv;
-  p.flags = (int)flags; p.scale = scale; p.ws = ws; p.stream = (hipStream_t)stream;
+  p.flags = (int)flags; p.scale = scale; p.ws = ws; p.ws_bytes = ws_bytes; p.stream = (hipStream_t)stream;
   return run_bwd(p);
 }
 

@@ -62,12 +62,12 @@ struct ColArgs {
   const int* cu;
   uint16_t* dk;
   uint16_t* dv;
-  const int* plan;      // [B * nkt][2]: parts of the key block (1 = not split), first slot
+  const int* plan;      // [B * nkt][2]: parts of the key block (1 = not split), first slot; NULL: none is split
   const int2* items;    // [B * nkt + capE]: (key block, part) work items, longest first; NULL: one per key block
   int* ctl;             // PlanCtl
   float* part;          // [capE * Hkv][2][kColKeys][D] fp32 partial dV, dK of split blocks
   int B, T, Hq, Hkv, G, nkt, ntok;
-  int capE;             // slots per KV head (0: no splitting)
+  int nq;               // work queues (queue_count)
   int varlen;
   int flags;            // as in RowArgs
   float scale_log2;
@@ -89,8 +89,11 @@ struct PlanCtl {
   int next[kCUs];
 };
 // One queue per KV head where the KV heads divide the CUs (workgroup w then
-// keeps to head w % Hkv, and with it an XCD to few heads), else one for all.
-__host__ __device__ __forceinline__ int queue_count(int Hkv) { return kCUs % Hkv == 0 ? Hkv : 1; }
+// keeps to head w % Hkv, and with it an XCD to few heads) and `bytes` hold
+// their counters, else one for all.
+static int queue_count(int Hkv, size_t bytes) {
+  return kCUs % Hkv == 0 && offsetof(PlanCtl, next) + Hkv * sizeof(int) <= bytes ? Hkv : 1;
+}
 
 // LSE / Delta layout: fixed [B][Hq][T], varlen [Hq][ntok].
 __device__ __forceinline__ long long lse_index(int varlen, int ntok, int Hq, int T, int b, int h, int tok0, int i) {
@@ -728,7 +731,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // (One workgroup per possible item left those without one to be started and
   // ended in turn behind the last items, as many as there are unused slots.)
   PlanCtl* ctl = reinterpret_cast<PlanCtl*>(a.ctl);
-  const int nq = queue_count(a.Hkv), queue = nq > 1 ? blockIdx.x % a.Hkv : 0;
+  const int nq = a.nq, queue = nq > 1 ? blockIdx.x % a.Hkv : 0;
   const int nitems = a.items ? ctl->nitems : a.B * a.nkt;
   const int nidx = nq > 1 ? nitems : nitems * a.Hkv;
   int idx = nq > 1 ? blockIdx.x / a.Hkv : blockIdx.x;
@@ -737,7 +740,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int g = nq > 1 ? queue : idx % a.Hkv;
   const int2 item = a.items ? a.items[nq > 1 ? idx : idx / a.Hkv] : make_int2(nq > 1 ? idx : idx / a.Hkv, 0);
   const int b = item.x / a.nkt, kt = item.x % a.nkt, chunk = item.y;
-  const int nchunk = a.items ? a.plan[2 * item.x] : 1, slot0 = a.items ? a.plan[2 * item.x + 1] : 0;
+  const int nchunk = a.plan ? a.plan[2 * item.x] : 1, slot0 = a.plan ? a.plan[2 * item.x + 1] : 0;
   const Trace tr = trace_of(a.cu, b, a.T, a.ntok);
   const int j0 = kt * kColKeys;
   if (j0 >= tr.L) break;   // only without a plan, where every workgroup has one item; the plan lists no such block
@@ -1030,7 +1033,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 // of 1/2 and 1/4 share and a threshold of 2/3 or 4/5 share: within 5% of that.
 __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict__ kstats, const int* __restrict__ cu,
                                                           int B, int T, int ntok, int nkt, int G, int Hkv, int capE,
-                                                          int grid, int* __restrict__ plan, int2* __restrict__ items,
+                                                          int grid, int nq, int* __restrict__ plan, int2* __restrict__ items,
                                                           int* __restrict__ split, PlanCtl* __restrict__ ctl) {
   constexpr int NBK = 2048, NW = 1024 / kWave;   // sort buckets, waves
   __shared__ int bucket[NBK];
@@ -1040,7 +1043,7 @@ __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict
   const int nblocks = B * nkt;
   bucket[tid] = bucket[tid + 1024] = 0;
   if (tid == 0) nsplit_s = 0;
-  if (tid < kCUs) ctl->next[tid] = grid / queue_count(Hkv);   // the first items are taken by index
+  if (tid < nq) ctl->next[tid] = grid / nq;   // the first items are taken by index
   const int per = (nblocks + 1023) / 1024;
   const int b0 = min(tid * per, nblocks), b1 = min(b0 + per, nblocks);
   // row-steps of a block: [j0/64, ceil(emax/64)); 0 past the trace
@@ -1107,8 +1110,10 @@ __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict
     const int steps = steps_of(blk), w = parts_of(steps);
     const bool grant = w > 0 && run + w <= capE;
     own_parts = grant ? w : 1;
-    plan[2 * blk] = own_parts;
-    plan[2 * blk + 1] = grant ? run : 0;
+    if (plan) {
+      plan[2 * blk] = own_parts;
+      plan[2 * blk + 1] = grant ? run : 0;
+    }
     if (grant) split[atomicAdd(&nsplit_s, 1)] = blk;
     run += w;
     if (steps == 0) continue;
@@ -1136,7 +1141,7 @@ __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict
   }
   __syncthreads();
   for (int blk = b0; blk < b1; ++blk) {
-    const int steps = steps_of(blk), nc = per == 1 ? own_parts : plan[2 * blk];
+    const int steps = steps_of(blk), nc = per == 1 ? own_parts : plan ? plan[2 * blk] : 1;
     if (steps == 0) continue;
     const int len = (steps + nc - 1) / nc;
     for (int c = 0; c < nc; ++c)
@@ -1251,13 +1256,12 @@ size_t ws_delta_bytes(int Hq, int ntok) { return 2 * (((size_t)Hq * ntok * sizeo
 
 static size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// Work plan of the column kernel: plan [B * nkt][2] int, work items
-// [B * nkt + capE] int2, partial sums [capE * Hkv][2][kColKeys][D] fp32.
-// capE: slots of parts per KV head, at most 2048 over all KV heads.  Up to
-// 2 * kSplitRowSteps row-steps only the CUs' shares ask for parts: kSplitShare
-// kCUs of them if every block is cut, and one more for each of at most kCUs cut
-// blocks.  None when no block can span more than two least parts.
-int split_cap(int B, int T, int Hkv, int G) {
+// Slots of parts per KV head that the plan can use, at most 2048 over all KV
+// heads.  Up to 2 * kSplitRowSteps row-steps only the CUs' shares ask for
+// parts: kSplitShare kCUs of them if every block is cut, and one more for each
+// of at most kCUs cut blocks.  None when no block can span more than two least
+// parts.
+static int split_cap(int B, int T, int Hkv, int G) {
   const long long max_span = (T + kQStep - 1) / kQStep, max_steps = max_span * G;
   if (max_steps <= 2 * kMinChunk) return 0;
   const long long nkt = (T + kColKeys - 1) / kColKeys;
@@ -1265,11 +1269,39 @@ int split_cap(int B, int T, int Hkv, int G) {
   const long long per_block = (max_steps + kMinChunk - 1) / kMinChunk;
   return (int)std::min<long long>(slots / Hkv, (long long)B * nkt * per_block);
 }
-size_t ws_split_bytes(int B, int T, int Hkv, int G, int D) {
-  const int capE = split_cap(B, T, Hkv, G);
-  const long long nkt = (T + kColKeys - 1) / kColKeys;
-  return round256((size_t)B * nkt * 2 * sizeof(int)) + round256(((size_t)B * nkt + capE) * sizeof(int2)) +
-         round256(sizeof(PlanCtl)) + round256((size_t)capE * sizeof(int)) + round256((size_t)capE * Hkv * 2 * kColKeys * D * sizeof(float));
+
+// Workspace of the column kernel for `cap` slots per KV head: plan [B * nkt][2]
+// int, work items [B * nkt + cap] int2, PlanCtl, the split blocks [cap] int,
+// partial sums [cap * Hkv][2][kColKeys][D] fp32.  Without slots no plan is
+// kept, and the counters (as many as fit) stand in its place.
+struct SplitSpace {
+  size_t plan, items, ctl, split, part;
+  size_t bytes() const { return plan + items + ctl + split + part; }
+};
+static SplitSpace split_space(int B, int T, int Hkv, int D, int cap) {
+  const size_t blocks = (size_t)B * ((T + kColKeys - 1) / kColKeys);
+  if (cap == 0) return {0, round256(blocks * sizeof(int2)), round256(blocks * 2 * sizeof(int)), 0, 0};
+  return {round256(blocks * 2 * sizeof(int)), round256((blocks + cap) * sizeof(int2)), round256(sizeof(PlanCtl)),
+          round256((size_t)cap * sizeof(int)), round256((size_t)cap * Hkv * 2 * kColKeys * D * sizeof(float))};
+}
+size_t ws_split_bytes(int B, int T, int Hkv, int G, int D) { return split_space(B, T, Hkv, D, split_cap(B, T, Hkv, G)).bytes(); }
+// The least a call takes: no partial sums up to 2 * kSplitRowSteps row-steps, beyond which a block that is not cut
+// would be the kernel's critical path.
+size_t ws_split_least(int B, int T, int Hkv, int D) {
+  const long long max_span = (T + kQStep - 1) / kQStep, nkt = (T + kColKeys - 1) / kColKeys;
+  const size_t whole = split_space(B, T, Hkv, D, 0).bytes();
+  if (max_span <= 2 * kSplitRowSteps) return whole;
+  const size_t cap = std::min<long long>(2048 / Hkv, B * nkt * ((max_span + kSplitRowSteps - 1) / kSplitRowSteps));
+  return whole - round256((size_t)B * nkt * sizeof(int2)) + round256(((size_t)B * nkt + cap) * sizeof(int2)) +
+         round256(cap * Hkv * 2 * kColKeys * D * sizeof(float));
+}
+// Slots per KV head in `bytes` of workspace: blocks that get none stay whole.
+static int split_fit(int B, int T, int Hkv, int G, int D, size_t bytes) {
+  int cap = split_cap(B, T, Hkv, G);
+  if (split_space(B, T, Hkv, D, cap).bytes() <= bytes) return cap;
+  cap = (int)std::min<size_t>(cap, bytes / ((size_t)Hkv * 2 * kColKeys * D * sizeof(float)));
+  while (cap > 0 && split_space(B, T, Hkv, D, cap).bytes() > bytes) --cap;
+  return cap;
 }
 static size_t half_delta_bytes(int Hq, int ntok) { return ws_delta_bytes(Hq, ntok) / 2; }
 
@@ -1344,7 +1376,8 @@ hipError_t launch_bwd_pre(const Problem& p, int2* kstats, float* delta) {
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* delta, void* split_ws) {
+hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* delta, void* split_ws,
+                           size_t split_bytes) {
   ColArgs a{};
   a.q = (const uint16_t*)p.q;
   a.k = (const uint16_t*)p.k;
@@ -1367,27 +1400,24 @@ hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* de
   a.flags = p.flags;
   a.scale = p.scale;
   a.scale_log2 = p.scale * 1.4426950408889634f;
-  a.capE = split_cap(p.B, p.T, p.Hkv, p.G);
-  int* split;   // split blocks
+  const int cap = split_fit(p.B, p.T, p.Hkv, p.G, p.D, split_bytes);
+  const SplitSpace sp = split_space(p.B, p.T, p.Hkv, p.D, cap);
   // one workgroup a CU, fewer if there cannot be as many items
-  const int grid = (int)std::min<long long>(kCUs, ((long long)a.nkt * p.B + a.capE) * p.Hkv);
-  {
-    char* w = (char*)split_ws;
-    int* plan = (int*)w;
-    w += round256((size_t)p.B * a.nkt * 2 * sizeof(int));
-    int2* items = (int2*)w;
-    w += round256(((size_t)p.B * a.nkt + a.capE) * sizeof(int2));
-    a.ctl = (int*)w;
-    w += round256(sizeof(PlanCtl));
-    split = (int*)w;
-    w += round256((size_t)a.capE * sizeof(int));
-    a.part = (float*)w;
-    // Without parts, and where every block starts at once, there is nothing to plan (5 us, and a launch).
-    if (a.capE == 0 && (long long)p.B * a.nkt * p.Hkv <= grid) plan = nullptr;
-    a.plan = plan;
-    a.items = plan ? items : nullptr;
-    if (plan) hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, p.stream, kstats, p.cu, p.B, p.T, p.ntok, a.nkt,
-                       p.G, p.Hkv, a.capE, grid, plan, items, split, (PlanCtl*)a.ctl);
+  const int grid = (int)std::min<long long>(kCUs, ((long long)a.nkt * p.B + cap) * p.Hkv);
+  char* w = (char*)split_ws;
+  int* plan = cap ? (int*)w : nullptr;
+  int2* items = (int2*)(w += sp.plan);
+  PlanCtl* ctl = (PlanCtl*)(w += sp.items);
+  int* split = (int*)(w += sp.ctl);   // split blocks
+  a.part = (float*)(w + sp.split);
+  a.nq = queue_count(p.Hkv, sp.ctl);
+  a.plan = plan;
+  // Without parts, and where every block starts at once, there is nothing to plan (5 us, and a launch).
+  if (cap > 0 || (long long)p.B * a.nkt * p.Hkv > grid) {
+    a.items = items;
+    a.ctl = (int*)ctl;
+    hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, p.stream, kstats, p.cu, p.B, p.T, p.ntok, a.nkt, p.G,
+                       p.Hkv, cap, grid, a.nq, plan, items, split, ctl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1396,12 +1426,12 @@ hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* de
   else hipLaunchKernelGGL(dkdv_kernel<64>, dim3(grid), dim3(512), 0, p.stream, a);
   prof_end(p.stream);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.capE == 0) return e;
+  if (e != hipSuccess || cap == 0) return e;
   if (p.D == 128)
-    hipLaunchKernelGGL(split_reduce_kernel<128>, dim3(kReduceGrid), dim3(256), 0, p.stream, (const PlanCtl*)a.ctl, a.plan, split, a.part, p.cu,
+    hipLaunchKernelGGL(split_reduce_kernel<128>, dim3(kReduceGrid), dim3(256), 0, p.stream, ctl, a.plan, split, a.part, p.cu,
                        (uint16_t*)p.dk, (uint16_t*)p.dv, p.B, p.T, p.ntok, a.nkt, p.Hkv, p.scale);
   else
-    hipLaunchKernelGGL(split_reduce_kernel<64>, dim3(kReduceGrid), dim3(256), 0, p.stream, (const PlanCtl*)a.ctl, a.plan, split, a.part, p.cu,
+    hipLaunchKernelGGL(split_reduce_kernel<64>, dim3(kReduceGrid), dim3(256), 0, p.stream, ctl, a.plan, split, a.part, p.cu,
                        (uint16_t*)p.dk, (uint16_t*)p.dv, p.B, p.T, p.ntok, a.nkt, p.Hkv, p.scale);
   return hipGetLastError();
 }

@@ -30,6 +30,7 @@ struct Problem {
   int flags;         // tile-classifier switches (kFlagNoEmptySkip, kFlagFullAsPartial); 0 normally
   float scale;
   void* ws;
+  size_t ws_bytes;   // backward
   hipStream_t stream;
 };
 
@@ -42,13 +43,15 @@ constexpr size_t kNoAllocScratchBytes = 256 * 1024;
 constexpr int kMaxDevices = 64;
 hipError_t noalloc_scratch(void** ptr);
 size_t ws_delta_bytes(int Hq, int ntok);
-size_t ws_split_bytes(int B, int T, int Hkv, int G, int D);
+size_t ws_split_bytes(int B, int T, int Hkv, int G, int D);   // that the dK/dV work plan can use
+size_t ws_split_least(int B, int T, int Hkv, int D);          // that it needs
 
 // Launchers.  Each returns the hipError_t of its launch(es).
 hipError_t launch_kstats(const Problem& p, int2* kstats);
 hipError_t launch_fwd(const Problem& p, const int2* kstats);
 hipError_t launch_bwd_pre(const Problem& p, int2* kstats, float* delta);   // and the key-tile statistics
-hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* delta, void* split_ws);
+hipError_t launch_bwd_dkdv(const Problem& p, const int2* kstats, const float* delta, void* split_ws,
+                           size_t split_bytes);
 hipError_t launch_bwd_dq(const Problem& p, const int2* kstats, const float* delta);
 hipError_t launch_classify(const int32_t* evict, const int32_t* cu, int B, int T, int BM, int BN,
                            uint8_t* out, hipStream_t stream);
