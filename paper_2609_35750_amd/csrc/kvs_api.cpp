@@ -618,7 +618,7 @@ static kvs_status_t check_decode_dims(int S, int Hq, int Hkv, int D, int num_blo
 
 size_t kvs_paged_decode_workspace(int num_seqs, int Hq, int Hkv, int D, int max_blocks, int block_size) {
   if (num_seqs < 1 || Hkv < 1 || max_blocks < 1 || block_size < 1) return 0;
-  return kvs::paged_ws_bytes(num_seqs, Hq, D, kvs::paged_units(num_seqs, Hkv, max_blocks, block_size, D));
+  return kvs::paged_ws_bytes(num_seqs, Hq, Hkv, max_blocks, block_size, D);
 }
 
 kvs_status_t kvs_paged_decode(const void* Q, const void* K_cache, const void* V_cache, const int32_t* slot_pos,
@@ -634,7 +634,7 @@ kvs_status_t kvs_paged_decode(const void* Q, const void* K_cache, const void* V_
   REQUIRE_PTR(V_cache, "V_cache");
   REQUIRE_PTR(O, "O");
   if (!slot_pos || !block_table || !seq_blocks || !LSE) return fail(KVS_ERR_NULL, "NULL table or output pointer");
-  const size_t need = kvs_paged_decode_workspace(num_seqs, Hq, Hkv, D, max_blocks, block_size);
+  const size_t need = kvs::paged_ws_least(num_seqs, Hq, Hkv, max_blocks, block_size, D);
   if (kvs_status_t st = check_ws(workspace, workspace_bytes, need)) return st;
   kvs::PagedDecode p{};
   p.q = Q;
@@ -654,6 +654,7 @@ kvs_status_t kvs_paged_decode(const void* Q, const void* K_cache, const void* V_
   p.num_blocks = num_blocks;
   p.scale = softmax_scale;
   p.ws = workspace;
+  p.ws_bytes = workspace_bytes;
   p.stream = (hipStream_t)stream;
   hipError_t e = kvs::launch_paged_decode(p);
   return e == hipSuccess ? KVS_OK : hip_fail(e, "paged decode launch");

@@ -45,6 +45,17 @@ inline int paged_units(int S, int Hkv, int max_blocks, int BS, int D) {
   return (int)std::min(std::max((round + Hkv - 1) / Hkv, S + slack), S * per_seq);
 }
 
+// Rows of partial results, per q-head.  A sequence of n units needs n of them if n > 1 and none if n = 1, and the
+// sequences before s have first - s units beyond their first: from row 2 (first - s) on it has 2 (n - 1) to itself.
+// Where that is less than a row for every unit, it saves the rows of the sequences that are not cut.
+__host__ __device__ __forceinline__ bool partials_paired(int S, int units) { return units < 2ll * S; }
+__host__ __device__ __forceinline__ int partial_units(int S, int units) {
+  return partials_paired(S, units) ? 2 * (units - S) : units;
+}
+__host__ __device__ __forceinline__ int partial_row(int S, int units, int s, int first) {
+  return partials_paired(S, units) ? 2 * (first - s) : first;
+}
+
 // 32-slot tiles of ns slots, as the plan counts them
 __host__ __device__ __forceinline__ int plan_tiles(int ns) {
   const unsigned t = ((unsigned)ns + kDecTile - 1) / kDecTile;

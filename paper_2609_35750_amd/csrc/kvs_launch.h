@@ -71,6 +71,7 @@ struct PagedDecode {
   int S, Hq, Hkv, D, max_blocks, block_size, num_blocks;
   float scale;
   void* ws;
+  size_t ws_bytes;
   hipStream_t stream;
 };
 // Slots of a host-held list as runs: |len| tokens from `tok` on, positions pos, pos + 1, ..., slots slot, slot + 1,
@@ -86,7 +87,8 @@ struct SlotRuns {
 hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
                                     int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
 hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
-size_t paged_ws_bytes(int S, int Hq, int D, int units);
+size_t paged_ws_bytes(int S, int Hq, int Hkv, int max_blocks, int BS, int D);   // that the decode can use
+size_t paged_ws_least(int S, int Hq, int Hkv, int max_blocks, int BS, int D);   // that it needs
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,
                                void* vc, int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
 hipError_t launch_paged_evict(const int* slots, int n, int* slot_pos, int num_slots, hipStream_t stream);

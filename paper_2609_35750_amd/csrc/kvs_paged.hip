@@ -103,11 +103,11 @@ struct DecodeArgs {
   const int* slot_pos;    // [num_blocks * BS]
   const int* table;       // [S][max_blocks]
   const int* nblk;        // [S]
-  // rows of the partials: units * Hq, sequence s from seq_units[s].x * Hq on as [q-head][its units]
+  // rows of the partials: partial_units * Hq, sequence s from partial_row * Hq on as [q-head][its units]
   float* part;            // [rows][D]: unnormalised O of each split (relative to its max)
   float2* part_ml;        // [rows]: max (log2 units), sum
   int plan;               // DecodePlan: how a wave finds its unit
-  int2* seq_units;        // kByWave: [S], first unit and number of units of the sequence
+  int2* seq_units;        // kByWave: [S], partial_row and number of units of the sequence
   int4* unit_seq;         // kListed: [units], sequence, its slots, its first unit, its units (0: no such unit)
   int* cut;               // kListed: number of cut sequences, their first units
   uint16_t* o;            // [S][Hq][D]: written here for sequences of one unit, by the merge for the others
@@ -115,6 +115,10 @@ struct DecodeArgs {
   int S, Hq, Hkv, G, max_blocks, BS, num_blocks, units;
   float scale_log2;       // softmax_scale * log2(e)
 };
+
+__device__ __forceinline__ int partial_row(const DecodeArgs& a, int s, int first) {
+  return partial_row(a.S, a.units, s, first);
+}
 
 // One unit a sequence; each wave plans by itself; looked up in unit_seq, which the plan kernel wrote.
 enum DecodePlan : int { kOneUnit = 0, kByWave = 1, kListed = 2 };
@@ -492,7 +496,7 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
     valid_q[R - 1] = 0u;
   }
 
-  if (a.plan == kByWave && lane == 0 && g == 0 && du.chunk == 0) a.seq_units[s] = make_int2(du.first, du.n);
+  if (a.plan == kByWave && lane == 0 && g == 0 && du.chunk == 0) a.seq_units[s] = make_int2(partial_row(a, s, du.first), du.n);
   const float l_tot = halves_sum(l_run);
   if (!col_ok) return;
   if (du.n == 1) {   // the sequence's only unit: O and LSE directly
@@ -509,7 +513,7 @@ __global__ void __launch_bounds__(64) paged_decode_kernel(DecodeArgs a) {
     return;
   }
   // partial of this unit for q-head column `col`
-  const size_t pidx = (size_t)du.first * a.Hq + (size_t)hcol * du.n + du.chunk;
+  const size_t pidx = (size_t)partial_row(a, s, du.first) * a.Hq + (size_t)hcol * du.n + du.chunk;
   float* dst = a.part + pidx * D;
   if (l_tot > 0.f) {   // an empty unit leaves its O unwritten (the merge skips it)
 #pragma unroll
@@ -617,7 +621,7 @@ __global__ void __launch_bounds__(64 * W) paged_combine_kernel(DecodeArgs a) {
   const int rows = a.cut[0] * a.Hq;
   for (int i = blockIdx.x; i < rows; i += gridDim.x) {
     const int4 m = a.unit_seq[a.cut[1 + i / a.Hq]];
-    combine_row<D, W>(a, m.x * a.Hq + i % a.Hq, make_int2(m.z, m.w));
+    combine_row<D, W>(a, m.x * a.Hq + i % a.Hq, make_int2(partial_row(a, m.x, m.z), m.w));
     __syncthreads();   // the next row's weights
   }
 }
@@ -666,10 +670,38 @@ hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_
 }
 
 static size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
-size_t paged_ws_bytes(int S, int Hq, int D, int units) {
-  const size_t rows = (size_t)units * Hq;
+// Partial results and what the waves and the merge look units up in; nothing for one unit a sequence.
+static size_t units_bytes(int S, int Hq, int D, int units) {
+  if (units <= S) return 0;
+  const size_t rows = (size_t)partial_units(S, units) * Hq;
   return round256(rows * D * sizeof(float)) + round256(rows * sizeof(float2)) + round256((size_t)S * sizeof(int2)) +
          round256((size_t)units * sizeof(int4));
+}
+// Partial results of equal splits, as many a sequence as make one round of waves, of four tiles of the table's width
+// at least.
+static size_t equal_splits_bytes(int S, int Hq, int Hkv, int max_blocks, int BS, int D) {
+  const long long waves = (long long)S * Hkv, most = std::max(1ll, (long long)max_blocks * BS / (4 * kDecTile));
+  const size_t rows = (size_t)S * Hq * std::min((decode_round(D) + waves - 1) / waves, most);
+  return round256(rows * D * sizeof(float)) + round256(rows * sizeof(float2));
+}
+// What the query gives; never less than equal splits took.
+size_t paged_ws_bytes(int S, int Hq, int Hkv, int max_blocks, int BS, int D) {
+  return std::max(units_bytes(S, Hq, D, paged_units(S, Hkv, max_blocks, BS, D)),
+                  equal_splits_bytes(S, Hq, Hkv, max_blocks, BS, D));
+}
+// At most `want` units that fit `bytes`.
+static int fitting_units(int S, int Hq, int D, int want, size_t bytes) {
+  while (want > S && units_bytes(S, Hq, D, want) > bytes) --want;
+  return want;
+}
+// The least a call takes: that of equal splits where it holds all but a sixteenth of the units (short of the query
+// by what they are looked up in), the query's size where it does not (narrow tables, whose units may be shorter than
+// four tiles).
+size_t paged_ws_least(int S, int Hq, int Hkv, int max_blocks, int BS, int D) {
+  const int want = paged_units(S, Hkv, max_blocks, BS, D);
+  const size_t equal = equal_splits_bytes(S, Hq, Hkv, max_blocks, BS, D);
+  return units_bytes(S, Hq, D, std::max(S, want - want / 16)) <= equal ? equal
+                                                                     : paged_ws_bytes(S, Hq, Hkv, max_blocks, BS, D);
 }
 
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,
@@ -736,10 +768,10 @@ hipError_t launch_paged_decode(const PagedDecode& p) {
   a.max_blocks = p.max_blocks;
   a.BS = p.block_size;
   a.num_blocks = p.num_blocks;
-  a.units = paged_units(p.S, p.Hkv, p.max_blocks, p.block_size, p.D);
+  a.units = fitting_units(p.S, p.Hq, p.D, paged_units(p.S, p.Hkv, p.max_blocks, p.block_size, p.D), p.ws_bytes);
   a.o = (uint16_t*)p.o;
   a.lse = p.lse;
-  const size_t rows = (size_t)a.units * p.Hq;
+  const size_t rows = (size_t)partial_units(p.S, a.units) * p.Hq;
   a.part = (float*)p.ws;
   a.part_ml = (float2*)((char*)p.ws + round256(rows * p.D * sizeof(float)));
   a.seq_units = (int2*)((char*)a.part_ml + round256(rows * sizeof(float2)));

@@ -4,6 +4,8 @@
 //    one), also with a reciprocal two units in the last place off;
 //  * together fit the grid and workspace that were sized for them, and those
 //    of one sequence the merge's list of 2,048;
+//  * have rows of partial results to themselves, inside the workspace, where
+//    a sequence is cut;
 //  * have the smallest size that fits, or one at most an eighth and one above
 //    it where the bisection stops at a sixteenth.
 // Prints "ok" and exits 0, or names the first failure.
@@ -82,6 +84,17 @@ int main() {
               return 1;
             }
             cut += n > S;
+            int first = 0, end = 0;   // first unit of the sequence; rows given out
+            for (int s = 0; s < S; ++s) {
+              const int m = kvs::unit_count(t[s], C, 1.f / (float)C), row = kvs::partial_row(S, units, s, first);
+              if (m > 1 && (row < end || row + m > kvs::partial_units(S, units))) {
+                std::printf("S %d Hkv %d D %d width %d kind %d: rows %d to %d of sequence %d\n", S, Hkv, D, width, kind,
+                            row, row + m, s);
+                return 1;
+              }
+              if (m > 1) end = row + m;
+              first += m;
+            }
             int lo = kvs::kMinTiles, hi = std::max(C, lo);   // smallest size that fits
             while (lo < hi) {
               const int c = lo + (hi - lo) / 2;
