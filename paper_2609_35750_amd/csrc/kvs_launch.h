@@ -75,7 +75,7 @@ struct PagedDecode {
   hipStream_t stream;
 };
 // Slots of a host-held list as runs: |len| tokens from `tok` on, positions pos, pos + 1, ..., slots slot, slot + 1,
-// ... (or slot, slot - 1, ... for len < 0).  Passed by value: 2 KB of launch arguments.
+// ... (or slot, slot - 1, ... for len < 0).  Passed by value: 2.5 KB of launch arguments.
 struct SlotRun {
   int tok, slot, pos, len;
 };
@@ -83,10 +83,25 @@ constexpr int kMaxRuns = 128;
 struct SlotRuns {
   int n;
   SlotRun r[kMaxRuns];
+  int first[kMaxRuns];   // workgroup the run begins with (share_runs)
 };
-hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
+// Shares the runs' work, per_tok items a token, out to workgroups of *items each: run i takes workgroups first[i] to
+// first[i + 1] - 1.  Returns their number.  A workgroup has 256 items, more if there would be more than 65,535 of them.
+inline unsigned share_runs(SlotRuns* runs, long long per_tok, long long* items) {
+  long long all = 0;
+  for (int i = 0; i < runs->n; ++i) all += (runs->r[i].len < 0 ? -(long long)runs->r[i].len : runs->r[i].len) * per_tok;
+  *items = 256 * ((all + 256ll * 65535 - 1) / (256ll * 65535) > 1 ? (all + 256ll * 65535 - 1) / (256ll * 65535) : 1);
+  unsigned wg = 0;
+  for (int i = 0; i < runs->n; ++i) {
+    const long long len = runs->r[i].len < 0 ? -(long long)runs->r[i].len : runs->r[i].len;
+    runs->first[i] = (int)wg;
+    wg += (unsigned)((len * per_tok + *items - 1) / *items);
+  }
+  return wg;
+}
+hipError_t launch_paged_append_runs(const void* kn, const void* vn, SlotRuns& runs, void* kc, void* vc,
                                     int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
-hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
+hipError_t launch_paged_evict_runs(SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
 size_t paged_ws_bytes(int S, int Hq, int Hkv, int max_blocks, int BS, int D);   // that the decode can use
 size_t paged_ws_least(int S, int Hq, int Hkv, int max_blocks, int BS, int D);   // that it needs
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,

@@ -62,18 +62,32 @@ __global__ void __launch_bounds__(256) paged_evict_kernel(const int* __restrict_
 
 // The same from slot lists the host holds, run by run: the slots a block manager
 // hands out lie in a few runs (a block's rows, and often blocks in a row), which
-// fit the launch's arguments, so nothing is uploaded.  blockIdx.y is the run.
-// Token i of a run: slot + i * step, position + i.
+// fit the launch's arguments, so nothing is uploaded.  Token i of a run: slot +
+// i * step, position + i.  A workgroup takes `items` of one run's items
+// (share_runs): with the longest run's number of workgroups for each, one long
+// run beside many short ones, which is what a fragmented free list hands out,
+// started up to 128 times that many, nearly all of them for nothing.
+__device__ __forceinline__ int run_of_workgroup(const SlotRuns& runs) {
+  if (runs.n == 1) return 0;
+  const int lane = threadIdx.x & 63;
+  int k = 0;   // runs that begin at or before this workgroup
+#pragma unroll
+  for (int h = 0; h < kMaxRuns; h += kWave)
+    k += __builtin_popcountll(__ballot(h + lane < runs.n && runs.first[h + lane] <= (int)blockIdx.x));
+  return __builtin_amdgcn_readfirstlane(k - 1);
+}
+
 template <int D>
 __global__ void __launch_bounds__(256) paged_append_runs_kernel(const uint16_t* __restrict__ kn,
                                                                 const uint16_t* __restrict__ vn, SlotRuns runs,
-                                                                uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
-                                                                int* __restrict__ slot_pos, int num_slots, int Hkv,
-                                                                int BS) {
-  const SlotRun run = runs.r[blockIdx.y];
+                                                                long long items, uint16_t* __restrict__ kc,
+                                                                uint16_t* __restrict__ vc, int* __restrict__ slot_pos,
+                                                                int num_slots, int Hkv, int BS) {
+  const int ri = run_of_workgroup(runs);
+  const SlotRun run = runs.r[ri];
   const long long per_tok = (long long)Hkv * (D / 8), chunks = (long long)(run.len < 0 ? -run.len : run.len) * per_tok;
-  for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < chunks;
-       c += (long long)gridDim.x * blockDim.x) {
+  const long long c0 = (blockIdx.x - runs.first[ri]) * items, c1 = min(c0 + items, chunks);
+  for (long long c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
     const long long i = c / per_tok, r = c - i * per_tok, src = ((long long)run.tok + i) * per_tok + r;
     const long long slot = run.slot + (run.len < 0 ? -i : i);
     if (slot < 0 || slot >= num_slots) continue;
@@ -85,12 +99,14 @@ __global__ void __launch_bounds__(256) paged_append_runs_kernel(const uint16_t* 
   }
 }
 
-__global__ void __launch_bounds__(256) paged_evict_runs_kernel(SlotRuns runs, int* __restrict__ slot_pos,
-                                                               int num_slots) {
-  const SlotRun run = runs.r[blockIdx.y];
-  const int n = run.len < 0 ? -run.len : run.len;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const long long slot = (long long)run.slot + (run.len < 0 ? -i : i);
+__global__ void __launch_bounds__(256) paged_evict_runs_kernel(SlotRuns runs, long long items,
+                                                               int* __restrict__ slot_pos, int num_slots) {
+  const int ri = run_of_workgroup(runs);
+  const SlotRun run = runs.r[ri];
+  const long long n = run.len < 0 ? -run.len : run.len;
+  const long long i0 = (blockIdx.x - runs.first[ri]) * items, i1 = min(i0 + items, n);
+  for (long long i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+    const long long slot = run.slot + (run.len < 0 ? -i : i);
     if (slot >= 0 && slot < num_slots) slot_pos[slot] = -1;
   }
 }
@@ -630,10 +646,10 @@ template __global__ void paged_append_kernel<64>(const uint16_t*, const uint16_t
                                                  uint16_t*, uint16_t*, int*, int, int, int);
 template __global__ void paged_append_kernel<128>(const uint16_t*, const uint16_t*, const int*, const int*, int,
                                                   uint16_t*, uint16_t*, int*, int, int, int);
-template __global__ void paged_append_runs_kernel<64>(const uint16_t*, const uint16_t*, SlotRuns, uint16_t*, uint16_t*,
-                                                      int*, int, int, int);
-template __global__ void paged_append_runs_kernel<128>(const uint16_t*, const uint16_t*, SlotRuns, uint16_t*,
-                                                       uint16_t*, int*, int, int, int);
+template __global__ void paged_append_runs_kernel<64>(const uint16_t*, const uint16_t*, SlotRuns, long long, uint16_t*,
+                                                      uint16_t*, int*, int, int, int);
+template __global__ void paged_append_runs_kernel<128>(const uint16_t*, const uint16_t*, SlotRuns, long long,
+                                                       uint16_t*, uint16_t*, int*, int, int, int);
 template __global__ void paged_decode_kernel<64>(DecodeArgs);
 template __global__ void paged_decode_kernel<128>(DecodeArgs);
 template __global__ void paged_combine_kernel<64, 1, false>(DecodeArgs);
@@ -646,26 +662,23 @@ template __global__ void paged_combine_kernel<64, 4, true>(DecodeArgs);
 template __global__ void paged_combine_kernel<128, 4, true>(DecodeArgs);
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
-                                    int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream) {
-  int longest = 1;
-  for (int i = 0; i < runs.n; ++i) longest = std::max(longest, std::abs(runs.r[i].len));
-  const long long chunks = (long long)longest * Hkv * (D / 8);
-  const dim3 grid((unsigned)std::min<long long>((chunks + 255) / 256, 4096), (unsigned)runs.n);
+hipError_t launch_paged_append_runs(const void* kn, const void* vn, SlotRuns& runs, void* kc, void* vc, int* slot_pos,
+                                    int num_slots, int BS, int Hkv, int D, hipStream_t stream) {
+  long long items = 0;
+  const dim3 grid(share_runs(&runs, (long long)Hkv * (D / 8), &items));
   if (D == 128)
     hipLaunchKernelGGL(paged_append_runs_kernel<128>, grid, dim3(256), 0, stream, (const uint16_t*)kn,
-                       (const uint16_t*)vn, runs, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
+                       (const uint16_t*)vn, runs, items, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
   else
     hipLaunchKernelGGL(paged_append_runs_kernel<64>, grid, dim3(256), 0, stream, (const uint16_t*)kn,
-                       (const uint16_t*)vn, runs, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
+                       (const uint16_t*)vn, runs, items, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
   return hipGetLastError();
 }
 
-hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream) {
-  int longest = 1;
-  for (int i = 0; i < runs.n; ++i) longest = std::max(longest, std::abs(runs.r[i].len));
-  const dim3 grid((unsigned)std::min((longest + 255) / 256, 4096), (unsigned)runs.n);
-  hipLaunchKernelGGL(paged_evict_runs_kernel, grid, dim3(256), 0, stream, runs, slot_pos, num_slots);
+hipError_t launch_paged_evict_runs(SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream) {
+  long long items = 0;
+  const dim3 grid(share_runs(&runs, 1, &items));
+  hipLaunchKernelGGL(paged_evict_runs_kernel, grid, dim3(256), 0, stream, runs, items, slot_pos, num_slots);
   return hipGetLastError();
 }
 

@@ -7,7 +7,8 @@ tile-classifier switches of the ``*_ex`` calls.  ``tests/host/stager_bounds.hip`
 checks the addressing of every staged tile: each LDS slot written once, every
 source read inside the trace's rows, and rows inside the trace copied
 unchanged through the swizzle.  ``tests/host/decode_plan.hip`` checks that the
-paged decode's units fit its grid and workspace."""
+paged decode's units fit its grid and workspace, ``tests/host/slot_runs.hip`` how
+the runs of a slot list are shared out to workgroups."""
 import os
 import shutil
 import subprocess
@@ -46,4 +47,10 @@ def test_tile_copy_addressing(tmp_path):
 @pytest.mark.skipif(HIPCC is None, reason="hipcc not available")
 def test_decode_units_fit(tmp_path):
     r = _build_and_run(tmp_path, "decode_plan.hip", "decode_plan")
+    assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr
+
+
+@pytest.mark.skipif(HIPCC is None, reason="hipcc not available")
+def test_slot_runs_shared_out(tmp_path):
+    r = _build_and_run(tmp_path, "slot_runs.hip", "slot_runs")
     assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr

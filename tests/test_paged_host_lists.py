@@ -101,6 +101,7 @@ LISTS = {
     "blocks": [16 * b + r for b in (5, 2, 9, 8) for r in range(16)],
     "zigzag": [10, 11, 10 + 5, 14, 13, 20, 22, 21, 23],
     "limit": [2 * i for i in range(512)],          # as many runs as the host call takes
+    "long and short": [1900 - 2 * i for i in range(90)] + list(range(1400)) + [1720, 1719, 1710] + list(range(1999, 1949, -1)),
     "out of range": [-1, 0, 1, 2045, 2046, 2047, 2048, 2049, (1 << 31) - 1],
 }
 
