@@ -83,21 +83,32 @@ constexpr int kMaxRuns = 128;
 struct SlotRuns {
   int n;
   SlotRun r[kMaxRuns];
-  int first[kMaxRuns];   // workgroup the run begins with (share_runs)
+  int first[kMaxRuns];   // RunGrid::items > 0: workgroup the run begins with
 };
-// Shares the runs' work, per_tok items a token, out to workgroups of *items each: run i takes workgroups first[i] to
-// first[i + 1] - 1.  Returns their number.  A workgroup has 256 items, more if there would be more than 65,535 of them.
-inline unsigned share_runs(SlotRuns* runs, long long per_tok, long long* items) {
-  long long all = 0;
-  for (int i = 0; i < runs->n; ++i) all += (runs->r[i].len < 0 ? -(long long)runs->r[i].len : runs->r[i].len) * per_tok;
-  *items = 256 * ((all + 256ll * 65535 - 1) / (256ll * 65535) > 1 ? (all + 256ll * 65535 - 1) / (256ll * 65535) : 1);
+// Grid of the run kernels, for per_tok items a token.  items = 0: workgroups x * 256 items of every run (y), in strides
+// of the grid.  Where runs of unequal length would leave more than half of those without any: items > 0, workgroups
+// first[i] to first[i + 1] - 1 are run i's, `items` of its items each (256, more beyond 65,535 workgroups).
+struct RunGrid {
+  unsigned x, y;
+  long long items;
+};
+inline RunGrid share_runs(SlotRuns* runs, long long per_tok) {
+  auto work = [&](int i) { return (runs->r[i].len < 0 ? -(long long)runs->r[i].len : runs->r[i].len) * per_tok; };
+  long long all = 0, longest = 0;
+  for (int i = 0; i < runs->n; ++i) {
+    all += work(i);
+    longest = work(i) > longest ? work(i) : longest;
+  }
+  const long long each = (longest + 255) / 256;
+  if (runs->n == 1 || each * runs->n <= 2 * ((all + 255) / 256 + runs->n))
+    return {(unsigned)(each < 4096 ? each : 4096), (unsigned)runs->n, 0};
+  const long long items = 256 * ((all + 256ll * 65535 - 1) / (256ll * 65535));
   unsigned wg = 0;
   for (int i = 0; i < runs->n; ++i) {
-    const long long len = runs->r[i].len < 0 ? -(long long)runs->r[i].len : runs->r[i].len;
     runs->first[i] = (int)wg;
-    wg += (unsigned)((len * per_tok + *items - 1) / *items);
+    wg += (unsigned)((work(i) + items - 1) / items);
   }
-  return wg;
+  return {wg, 1, items};
 }
 hipError_t launch_paged_append_runs(const void* kn, const void* vn, SlotRuns& runs, void* kc, void* vc,
                                     int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);

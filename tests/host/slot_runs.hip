@@ -1,7 +1,7 @@
 // Host build of the sharing of slot runs (share_runs): every item of every run
-// belongs to exactly one workgroup, found as the kernels find it (the last run
-// that begins at or before it), no workgroup is without items, and there are no
-// more of them than the runs' work asks for, however unequal the runs are.
+// belongs to exactly one workgroup, found as the kernels find it (blockIdx.y, or
+// the last run that begins at or before it), and there are no more workgroups
+// than twice the runs' work asks for, however unequal the runs are.
 // Prints "ok" and exits 0, or names the first failure.
 #include <algorithm>
 #include <cstdio>
@@ -11,30 +11,37 @@
 #include "kvs_launch.h"
 
 static int check(kvs::SlotRuns& runs, long long per_tok) {
-  long long items = 0, all = 0, need = 0;
-  const unsigned grid = kvs::share_runs(&runs, per_tok, &items);
+  const kvs::RunGrid g = kvs::share_runs(&runs, per_tok);
+  auto work = [&](int i) { return std::abs((long long)runs.r[i].len) * per_tok; };
+  long long all = 0, need = 0, given = 0;
   for (int i = 0; i < runs.n; ++i) {
-    const long long work = std::abs((long long)runs.r[i].len) * per_tok;
-    all += work;
-    need += (work + items - 1) / items;
+    all += work(i);
+    need += (work(i) + 255) / 256;
   }
-  if (grid != need || grid > 65535u + runs.n || (all <= 256ll * 65535 && items != 256)) {
-    std::printf("%d runs, %lld items: %u workgroups of %lld\n", runs.n, all, grid, items);
+  const long long grid = (long long)g.x * g.y;
+  if (g.x < 1 || g.y < 1 || grid > 2 * need + 2 * runs.n || grid > 65535ll * 9 + runs.n) {
+    std::printf("%d runs, %lld items: %u x %u workgroups of %lld\n", runs.n, all, g.x, g.y, g.items);
     return 1;
   }
-  long long given = 0;
+  if (g.items == 0) {   // strides of the grid: every run has its workgroups
+    if (g.y != (unsigned)runs.n) {
+      std::printf("%d runs, %u rows of workgroups\n", runs.n, g.y);
+      return 1;
+    }
+    return 0;
+  }
   int last = -1;
-  for (unsigned wg = 0; wg < grid; ++wg) {
+  for (unsigned wg = 0; wg < g.x; ++wg) {
     int k = 0;
     for (int i = 0; i < runs.n; ++i) k += runs.first[i] <= (int)wg;
     --k;
-    const long long work = std::abs((long long)runs.r[k].len) * per_tok, c0 = (wg - runs.first[k]) * items;
-    if (k < last || c0 >= work) {
-      std::printf("workgroup %u of %u: run %d, item %lld of %lld\n", wg, grid, k, c0, work);
+    const long long c0 = (wg - runs.first[k]) * g.items;
+    if (k < last || c0 >= work(k)) {
+      std::printf("workgroup %u of %u: run %d, item %lld of %lld\n", wg, g.x, k, c0, work(k));
       return 1;
     }
     last = k;
-    given += std::min(items, work - c0);
+    given += std::min(g.items, work(k) - c0);
   }
   if (given != all) {
     std::printf("%lld of %lld items given out\n", given, all);
