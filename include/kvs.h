@@ -325,8 +325,10 @@ kvs_status_t kvs_paged_evict(const int32_t* slots, int n, int32_t* slot_pos, int
  * and kvs_bm_evict give), which are read before the call returns: the slots
  * travel as runs in the launch's arguments and nothing is uploaded.  Lists
  * that lie in too many runs (more than 512; consecutive slots up or down, and
- * for the append consecutive positions, make a run) give KVS_ERR_UNSUPPORTED
- * before any work is enqueued: use the calls above. */
+ * for the append consecutive positions, make a run), and a stream that is being
+ * captured (a replay would write the same slots again, whoever holds them by
+ * then), give KVS_ERR_UNSUPPORTED before any work is enqueued: use the calls
+ * above. */
 kvs_status_t kvs_paged_append_host(const void* K_new, const void* V_new, const int32_t* positions,
                                    const int32_t* slots, int n, void* K_cache, void* V_cache, int32_t* slot_pos,
                                    int num_blocks, int block_size, int Hkv, int D, void* stream);

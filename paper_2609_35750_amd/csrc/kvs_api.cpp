@@ -558,6 +558,12 @@ static bool count_runs(const int32_t* pos, const int32_t* slots, int n) {
   return t == n;
 }
 
+// A captured launch would write its recorded slots again at every replay, whoever holds them by then.
+static bool capturing(void* stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing((hipStream_t)stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 kvs_status_t kvs_paged_append_host(const void* K_new, const void* V_new, const int32_t* positions,
                                    const int32_t* slots, int n, void* K_cache, void* V_cache, int32_t* slot_pos,
                                    int num_blocks, int block_size, int Hkv, int D, void* stream) {
@@ -572,6 +578,7 @@ kvs_status_t kvs_paged_append_host(const void* K_new, const void* V_new, const i
   REQUIRE_PTR(K_new, "K_new");
   REQUIRE_PTR(V_new, "V_new");
   if (!positions || !slots) return fail(KVS_ERR_NULL, "positions or slots is NULL");
+  if (capturing(stream)) return fail(KVS_ERR_UNSUPPORTED, "host lists are not captured");
   if (!count_runs(positions, slots, n)) return fail(KVS_ERR_UNSUPPORTED, "slots lie in too many runs");
   kvs::SlotRuns runs;
   for (int t = 0; t < n;) {
@@ -591,6 +598,7 @@ kvs_status_t kvs_paged_evict_host(const int32_t* slots, int n, int32_t* slot_pos
   if (!slot_pos) return fail(KVS_ERR_NULL, "slot_pos is NULL");
   if (n == 0) return KVS_OK;
   if (!slots) return fail(KVS_ERR_NULL, "slots is NULL");
+  if (capturing(stream)) return fail(KVS_ERR_UNSUPPORTED, "host lists are not captured");
   if (!count_runs(nullptr, slots, n)) return fail(KVS_ERR_UNSUPPORTED, "slots lie in too many runs");
   kvs::SlotRuns runs;
   for (int t = 0; t < n;) {

@@ -145,7 +145,7 @@ class PagedKVCache:
             st = lib.kvs_paged_append_host(_ptr(k_new), _ptr(v_new), _np_ptr(pos), _np_ptr(slots), pos.size,
                                            _ptr(self.k), _ptr(self.v), _ptr(self.slot_pos), self.num_blocks,
                                            self.block_size, self.Hkv, self.D, _stream(self.k))
-            if st == KVS_ERR_UNSUPPORTED:   # too many runs of slots for the launch's arguments
+            if st == KVS_ERR_UNSUPPORTED:   # too many runs of slots for the launch's arguments, or under capture
                 kvs_paged_append(k_new, v_new, torch.from_numpy(pos).to(self.device),
                                  torch.from_numpy(slots).to(self.device), self.k, self.v, self.slot_pos,
                                  self.block_size)

@@ -162,3 +162,35 @@ def test_too_many_runs_fall_back():
     np.testing.assert_array_equal(got, kn.view(torch.int16).cpu().numpy())
     cache.evict(0, np.random.default_rng(4).permutation(np.arange(5000, 5000 + order.size)))
     assert (cache.slot_pos.cpu().numpy()[slots] == -1).all()
+
+
+@pytest.mark.gpu
+def test_host_lists_are_not_captured():
+    """A list the host holds is refused by a capturing stream, and a replay changes nothing."""
+    from paper_2609_35750_amd import kvs
+
+    dev, lib = torch.device("cuda:0"), kvs.lib
+    Hkv, D, bs, nb, n = 2, 64, 16, 8, 20
+    slots, pos = np.arange(n, dtype=np.int32), np.arange(n, dtype=np.int32)
+    kn = torch.ones((n, Hkv, D), dtype=torch.bfloat16, device=dev)
+    k, v = (torch.zeros((nb, Hkv, bs, D), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    sp = torch.full((nb * bs,), -1, dtype=torch.int32, device=dev)
+    count = torch.zeros(1, device=dev)
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)   # noqa: E731
+
+    def both():
+        stream = torch.cuda.current_stream().cuda_stream
+        return (lib.kvs_paged_append_host(kn.data_ptr(), kn.data_ptr(), p(pos), p(slots), n, k.data_ptr(),
+                                          v.data_ptr(), sp.data_ptr(), nb, bs, Hkv, D, stream),
+                lib.kvs_paged_evict_host(p(slots), n, sp.data_ptr(), nb, bs, stream))
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        count += 1
+        st = both()
+    assert st == (kvs.KVS_ERR_UNSUPPORTED, kvs.KVS_ERR_UNSUPPORTED)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+    assert count.item() == 3 and (k == 0).all() and (sp == -1).all()
+    assert both() == (kvs.KVS_OK, kvs.KVS_OK)
