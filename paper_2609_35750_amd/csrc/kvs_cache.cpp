@@ -10,7 +10,9 @@
 #include "kvs_cache.h"
 
 #include <algorithm>
+#include <climits>
 #include <cstdio>
+#include <new>
 
 namespace kvs {
 
@@ -75,8 +77,8 @@ static int fail_msg(std::string* err, int code, const char* msg, long long a = 0
 int BlockManager::append(int seq, const int32_t* pos, int n, int32_t* slots, std::string* err) {
   if (seq < 0 || seq >= ns_) return fail_msg(err, kBadArg, "sequence index %lld out of range", seq);
   auto& map = slot_of_[seq];
-  // Reserve every position first (a marker no slot has), counted as live so that its page stays; a failure
-  // takes the markers back.
+  // Reserve every position first (a marker no slot has), counted as live so that its page stays, and room for the
+  // new blocks; a failure, of an allocation too, takes the markers back.
   constexpr int kReserved = -2;
   int done = 0, code = kOk;
   for (; done < n; ++done) {
@@ -85,7 +87,13 @@ int BlockManager::append(int seq, const int32_t* pos, int n, int32_t* slots, std
       code = fail_msg(err, kBadArg, "negative trace position %lld", p);
       break;
     }
-    int* s = map.make(p);
+    int* s = nullptr;
+    try {
+      s = map.make(p);
+    } catch (const std::bad_alloc&) {
+      code = fail_msg(err, kCapacity, "out of host memory at trace position %lld", p);
+      break;
+    }
     if (*s != SlotMap::kNone) {
       code = fail_msg(err, kBadState, "trace position %lld is already in the cache", p);
       break;
@@ -100,6 +108,11 @@ int BlockManager::append(int seq, const int32_t* pos, int n, int32_t* slots, std
     code = fail_msg(err, kCapacity, "out of cache blocks (%lld more needed)", need);
   if (code == kOk && (long long)blocks_[seq].size() + need > mb_)
     code = fail_msg(err, kCapacity, "sequence would hold more than max_blocks (%lld) blocks", mb_);
+  if (code == kOk) try {
+      blocks_[seq].reserve(blocks_[seq].size() + need);
+    } catch (const std::bad_alloc&) {
+      code = fail_msg(err, kCapacity, "out of host memory for %lld blocks", need);
+    }
   if (code != kOk) {
     for (int i = 0; i < done; ++i) {
       *map.find(pos[i]) = SlotMap::kNone;
@@ -133,27 +146,27 @@ void BlockManager::drop_block(int seq, int blk) {
 int BlockManager::evict(int seq, const int32_t* pos, int n, int32_t* slots, std::string* err) {
   if (seq < 0 || seq >= ns_) return fail_msg(err, kBadArg, "sequence index %lld out of range", seq);
   auto& map = slot_of_[seq];
-  // Mark every entry as taken first (its slot s >= 0 as kTaken - s), so that a repeated position shows; a failure
-  // takes the marks back.
-  constexpr int kTaken = -3;
+  // Mark every entry as taken first (the sign bit of its slot; no slot gives kNone), so that a repeated position
+  // shows; a failure takes the marks back.
+  constexpr int kTaken = INT_MIN;
   for (int i = 0; i < n; ++i) {
     int* s = pos[i] < 0 ? nullptr : map.find(pos[i]);
     if (!s || *s < 0) {
-      const int code = s && *s <= kTaken
+      const int code = s && *s != SlotMap::kNone
                            ? fail_msg(err, kBadState, "trace position %lld evicted twice", pos[i])
                            : fail_msg(err, kBadState, "trace position %lld is not in the cache", pos[i]);
       while (--i >= 0) {
         int* t = map.find(pos[i]);
-        *t = kTaken - *t;
+        *t ^= kTaken;
       }
       return code;
     }
-    *s = kTaken - *s;
+    *s ^= kTaken;
   }
   for (int i = 0; i < n; ++i) {
     const int p = pos[i];
     int* s = map.find(p);
-    const int slot = kTaken - *s;
+    const int slot = *s ^ kTaken;
     *s = SlotMap::kNone;
     map.count(p, -1);
     slots[i] = slot;

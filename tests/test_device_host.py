@@ -54,3 +54,14 @@ def test_decode_units_fit(tmp_path):
 def test_slot_runs_shared_out(tmp_path):
     r = _build_and_run(tmp_path, "slot_runs.hip", "slot_runs")
     assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_block_manager_out_of_memory(tmp_path):
+    """Host only: a failed allocation in an append gives an error and leaves the manager as it was."""
+    exe = str(tmp_path / "bm_memory")
+    csrc = os.path.join(ROOT, "paper_2609_35750_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, os.path.join(ROOT, "tests", "host", "bm_memory.cpp"),
+                    os.path.join(csrc, "kvs_cache.cpp"), "-o", exe], check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr
