@@ -1361,8 +1361,13 @@ hipError_t launch_bwd_pre(const Problem& p, int2* kstats, float* delta) {
   if (p.B > kMaxTraces) return hipErrorInvalidConfiguration;
   const long long rows = (long long)p.ntok * p.Hq;
   float* lse2 = (float*)((char*)delta + half_delta_bytes(p.Hq, p.ntok));
-  const int nks = kstats_groups(p.T) * p.B;
-  dim3 grid((unsigned)((rows + 15) / 16 + nks)), block(256);
+  const PreGrid pg = bwd_pre_grid(rows, (long long)kstats_groups(p.T) * p.B);
+  if (!pg.with_kstats) {
+    hipError_t e = launch_kstats(p, kstats);
+    if (e != hipSuccess) return e;
+  }
+  const int nks = pg.with_kstats ? kstats_groups(p.T) * p.B : 0;
+  dim3 grid(pg.blocks), block(256);
   prof_begin("bwd_pre", p.stream);
   if (p.D == 128)
     hipLaunchKernelGGL(bwd_pre_kernel<128>, grid, block, 0, p.stream, (const uint16_t*)p.o_in,

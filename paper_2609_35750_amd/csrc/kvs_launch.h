@@ -46,6 +46,18 @@ size_t ws_delta_bytes(int Hq, int ntok);
 size_t ws_split_bytes(int B, int T, int Hkv, int G, int D);   // that the dK/dV work plan can use
 size_t ws_split_least(int B, int T, int Hkv, int D);          // that it needs
 
+// Grid of the backward's preprocess: 16 rows a workgroup of 256 threads, and the workgroups of the key-tile statistics
+// in front of them where a launch, of at most 2^32 - 1 threads, holds both.
+struct PreGrid {
+  unsigned blocks;
+  bool with_kstats;
+};
+inline PreGrid bwd_pre_grid(long long rows, long long kstats_blocks) {
+  const long long blocks = (rows + 15) / 16;
+  const bool both = (blocks + kstats_blocks) * 256 <= 0xffffffffll;
+  return {(unsigned)(both ? blocks + kstats_blocks : blocks), both};
+}
+
 // Launchers.  Each returns the hipError_t of its launch(es).
 hipError_t launch_kstats(const Problem& p, int2* kstats);
 hipError_t launch_fwd(const Problem& p, const int2* kstats);

@@ -1,7 +1,9 @@
-// Host build of the sharing of slot runs (share_runs): every item of every run
+// Host build of two launch grids.  Slot runs (share_runs): every item of every run
 // belongs to exactly one workgroup, found as the kernels find it (blockIdx.y, or
 // the last run that begins at or before it), and there are no more workgroups
-// than twice the runs' work asks for, however unequal the runs are.
+// than twice the runs' work asks for, however unequal the runs are.  And the
+// grid of the backward's preprocess: it takes every number of rows that fits a
+// launch by itself, with the key-tile statistics only where they fit as well.
 // Prints "ok" and exits 0, or names the first failure.
 #include <algorithm>
 #include <cstdio>
@@ -64,6 +66,15 @@ int main() {
     if (it % 500 == 0) runs.r[0].len = 0x7fffffff;
     if (check(runs, it % 2 ? 1 : 8 * (1 + rng() % 16))) return 1;
   }
+  const long long most = 0xffffffffll / 256;   // workgroups of a launch
+  for (long long blocks : {1ll, 1000ll, most - 5, most - 1, most})
+    for (long long ks : {1ll, 2ll, 4ll, 5ll, 6ll, 4096ll, most}) {
+      const kvs::PreGrid g = kvs::bwd_pre_grid(16 * blocks, ks);
+      if (g.with_kstats != (blocks + ks <= most) || g.blocks != blocks + (g.with_kstats ? ks : 0) || g.blocks > most) {
+        std::printf("%lld row and %lld statistics workgroups: %u, %d\n", blocks, ks, g.blocks, g.with_kstats);
+        return 1;
+      }
+    }
   std::printf("ok\n");
   return 0;
 }

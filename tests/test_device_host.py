@@ -7,8 +7,9 @@ tile-classifier switches of the ``*_ex`` calls.  ``tests/host/stager_bounds.hip`
 checks the addressing of every staged tile: each LDS slot written once, every
 source read inside the trace's rows, and rows inside the trace copied
 unchanged through the swizzle.  ``tests/host/decode_plan.hip`` checks that the
-paged decode's units fit its grid and workspace, ``tests/host/slot_runs.hip`` how
-the runs of a slot list are shared out to workgroups."""
+paged decode's units fit its grid and workspace, ``tests/host/launch_grids.hip`` how
+the runs of a slot list are shared out to workgroups and the limit of the
+backward's preprocess."""
 import os
 import shutil
 import subprocess
@@ -51,8 +52,8 @@ def test_decode_units_fit(tmp_path):
 
 
 @pytest.mark.skipif(HIPCC is None, reason="hipcc not available")
-def test_slot_runs_shared_out(tmp_path):
-    r = _build_and_run(tmp_path, "slot_runs.hip", "slot_runs")
+def test_launch_grids(tmp_path):
+    r = _build_and_run(tmp_path, "launch_grids.hip", "launch_grids")
     assert r.returncode == 0 and r.stdout.rstrip().endswith("ok"), r.stdout + r.stderr
 
 
