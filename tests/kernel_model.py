@@ -17,11 +17,9 @@ number formats instead of guessing it:
 * backward preprocess: ``Delta = sum(O_bf16 * dO)`` in fp32 and
   ``LSE * log2 e`` in fp32;
 * dK/dV kernel: ``P = exp2(S * scale * log2 e - LSE * log2 e)`` in fp32,
-  rounded to bf16 for ``dV += P^T dO``; ``dS = P (dP - Delta)`` (fp32 product,
-  rounded to bf16), ``dK += dS^T Q``; outputs ``bf16(dV)``, ``bf16(dK * scale)``.
-  The model rounds this second P to fp16, as a kernel that passes it through
-  LDS does; the kernel multiplies by the fp32 P, so the modelled dK error bounds
-  its own from above;
+  rounded to bf16 for ``dV += P^T dO``; ``dS = P (dP - Delta)`` (product of the
+  unrounded P in fp32, rounded to bf16), ``dK += dS^T Q``; outputs ``bf16(dV)``,
+  ``bf16(dK * scale)``;
 * dQ kernel: the same fp32 ``P`` unrounded, ``dS = bf16(P (dP - Delta))``,
   ``dQ = bf16((dS K) * scale)``.
 
@@ -54,10 +52,6 @@ def bf16(x):
     if special.any():
         out = np.where(special, a.astype(np.float64), out)
     return out
-
-
-def f16(x):
-    return np.asarray(x, dtype=np.float64).astype(np.float16).astype(np.float64)
 
 
 def ulp_bf16(x):
@@ -151,7 +145,7 @@ def backward_trace(q, k, v, e, scale, do, O, LSE):
         P = np.where(vis, f32(np.exp2(np.where(vis, x, 0.0))), 0.0)
         dP = f32(do[:, h] @ v[:, g].T - delta[:, h][:, None])
         dv_acc[:, g] = f32(dv_acc[:, g] + bf16(P).T @ do[:, h])
-        dk_acc[:, g] = f32(dk_acc[:, g] + bf16(f32(f16(P) * dP)).T @ q[:, h])
+        dk_acc[:, g] = f32(dk_acc[:, g] + bf16(f32(P * dP)).T @ q[:, h])
         dq[:, h] = bf16(f32(f32(bf16(f32(P * dP)) @ k[:, g]) * scale))
     return dq, bf16(f32(dk_acc * scale)), bf16(dv_acc)
 
@@ -188,9 +182,8 @@ def excess_ulps(x, ref, flat=2e-2):
 
 
 def math_check():
-    """Sanity of the rounding helpers against numbers whose bf16 / fp16 forms are known."""
+    """Sanity of the rounding helpers against numbers whose bf16 forms are known."""
     assert bf16(1.0 + 2.0 ** -8) == 1.0            # tie -> even
     assert bf16(1.0 + 3 * 2.0 ** -9) == 1.0 + 2.0 ** -7
-    assert f16(1.0 + 2.0 ** -11) == 1.0
     assert ulp_bf16(27.0) == 0.125 and ulp_bf16(1.0) == 2.0 ** -7 and ulp_bf16(0.75) == 2.0 ** -8
     assert math.isnan(float(bf16(np.nan))) and bf16(-np.inf) == -np.inf
