@@ -84,6 +84,8 @@ int main() {
   if (check<64, 64, 4, true>("dQ K/V tile, D=64")) return 1;
   if (check<128, 64, 8, false>("dK/dV Q/dO tile, D=128")) return 1;
   if (check<64, 64, 8, false>("dK/dV Q/dO tile, D=64")) return 1;
+  if (check<128, 128, 8, true>("dK/dV V tile, D=128")) return 1;
+  if (check<64, 128, 8, true>("dK/dV V tile, D=64")) return 1;
   std::printf("ok\n");
   return 0;
 }
