@@ -342,12 +342,8 @@ struct RowStager {
   }
 };
 
-// 64 consecutive 4-byte values (clamped at index imax) into LDS, by one wave.
-__device__ __forceinline__ void stage_words(uint32_t lds, const void* __restrict__ g, int i0, int imax, int lane) {
-  const char* base = uniform_ptr((const char*)g + 4ll * i0);
-  dma_b32(base, 4u * (uint32_t)(min(i0 + lane, imax) - i0), lds);
-}
-// the same from the address of the first value (wave-uniform), dmax more values being valid
+// 64 consecutive 4-byte values into LDS by one wave, from the (wave-uniform) address of the first; dmax more of them
+// are valid, and the lanes beyond repeat the last one.
 __device__ __forceinline__ void stage_words_at(uint32_t lds, const void* base, int dmax, int lane) {
   dma_b32(base, 4u * (uint32_t)min(lane, dmax), lds);
 }
