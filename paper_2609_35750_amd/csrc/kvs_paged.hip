@@ -214,6 +214,59 @@ __device__ __forceinline__ int quick_div(int x, int y) {
 // slots of the blocks sequence s uses (clamped to the table width; some may be evicted)
 __device__ __forceinline__ int slots_of(const DecodeArgs& a, int s) { return min(max(a.nblk[s], 0), a.max_blocks) * a.BS; }
 
+// The unit u of up to 64 REGS sequences: its sequence, that one's slots, first unit and units.  False past the last one.
+template <int REGS>
+__device__ __forceinline__ bool plan_by_wave(const DecodeArgs& a, int u, int lane, int& s, int& ns, int& first, int& n) {
+  int sl[REGS];   // slots of sequences 64 k + lane; -1: none
+#pragma unroll
+  for (int k = 0; k < REGS; ++k) {
+    const int i = k * kWave + lane;
+    sl[k] = k * kWave < a.S ? slots_of(a, min(i, a.S - 1)) : -1;
+    if (i >= a.S) sl[k] = -1;
+  }
+  int sum = 0, top = 0;   // at most 2^28
+#pragma unroll
+  for (int k = 0; k < REGS; ++k) {
+    const int t = plan_tiles(max(sl[k], 0));
+    sum += t;
+    top = max(top, t);
+  }
+  const int total = wave_last(wave_scan(sum));
+  auto count = [&](int slots, int c, float rc) __attribute__((always_inline)) {
+    return slots < 0 ? 0 : unit_count(plan_tiles(slots), c, rc);
+  };
+  auto units_at = [&](int c) __attribute__((always_inline)) {
+    const float rc = __builtin_amdgcn_rcpf((float)c);
+    int m = 0;
+#pragma unroll
+    for (int k = 0; k < REGS; ++k)
+      if (k * kWave < a.S) m += count(sl[k], c, rc);
+    return wave_last(wave_scan(m));
+  };
+  auto upper = [&]() __attribute__((always_inline)) {
+    return min(wave_max(top), quick_div(total, a.units - a.S) + 1);
+  };
+  const int C = unit_size(quick_div(max(total - 1, 0), a.units) + 1, a.units, 30, units_at, upper);
+  const float rc = __builtin_amdgcn_rcpf((float)C);
+  int base = 0, l = -1;
+#pragma unroll
+  for (int k = 0; k < REGS; ++k) {
+    if (k * kWave < a.S && l < 0) {
+      const int m = count(sl[k], C, rc), incl = wave_scan(m);
+      const unsigned long long hit = __ballot(u < base + incl);
+      if (hit != 0ull) {
+        l = __builtin_ctzll(hit);
+        s = k * kWave + l;
+        ns = __builtin_amdgcn_readlane(sl[k], l);
+        n = __builtin_amdgcn_readlane(m, l);
+        first = base + __builtin_amdgcn_readlane(incl, l) - n;
+      }
+      base += wave_last(incl);
+    }
+  }
+  return l >= 0;
+}
+
 // The unit and KV head of workgroup `wg`; s = -1 past the last one.  All lanes
 // of the wave take part.  A sequence's workgroups are consecutive, its units
 // fastest, then the KV heads.
@@ -226,55 +279,8 @@ __device__ __forceinline__ DecodeUnit decode_unit(const DecodeArgs& a, int wg, i
     const int4 m = a.unit_seq[__builtin_amdgcn_readfirstlane(u)];
     s = m.x, ns = m.y, first = m.z, n = m.w;
     if (n == 0) return {-1, 0, 0, 0, 0};
-  } else {
-    int sl[kPlanRegs];   // slots of sequences 64 k + lane; -1: none
-#pragma unroll
-    for (int k = 0; k < kPlanRegs; ++k) {
-      const int i = k * kWave + lane;
-      sl[k] = k * kWave < a.S ? slots_of(a, min(i, a.S - 1)) : -1;
-      if (i >= a.S) sl[k] = -1;
-    }
-    int sum = 0, top = 0;   // at most 2^28
-#pragma unroll
-    for (int k = 0; k < kPlanRegs; ++k) {
-      const int t = plan_tiles(max(sl[k], 0));
-      sum += t;
-      top = max(top, t);
-    }
-    const int total = wave_last(wave_scan(sum));
-    auto count = [&](int slots, int c, float rc) __attribute__((always_inline)) {
-      return slots < 0 ? 0 : unit_count(plan_tiles(slots), c, rc);
-    };
-    auto units_at = [&](int c) __attribute__((always_inline)) {
-      const float rc = __builtin_amdgcn_rcpf((float)c);
-      int m = 0;
-#pragma unroll
-      for (int k = 0; k < kPlanRegs; ++k)
-        if (k * kWave < a.S) m += count(sl[k], c, rc);
-      return wave_last(wave_scan(m));
-    };
-    auto upper = [&]() __attribute__((always_inline)) {
-      return min(wave_max(top), quick_div(total, a.units - a.S) + 1);
-    };
-    const int C = unit_size(quick_div(max(total - 1, 0), a.units) + 1, a.units, 30, units_at, upper);
-    const float rc = __builtin_amdgcn_rcpf((float)C);
-    int base = 0, l = -1;
-#pragma unroll
-    for (int k = 0; k < kPlanRegs; ++k) {
-      if (k * kWave < a.S && l < 0) {
-        const int m = count(sl[k], C, rc), incl = wave_scan(m);
-        const unsigned long long hit = __ballot(u < base + incl);
-        if (hit != 0ull) {
-          l = __builtin_ctzll(hit);
-          s = k * kWave + l;
-          ns = __builtin_amdgcn_readlane(sl[k], l);
-          n = __builtin_amdgcn_readlane(m, l);
-          first = base + __builtin_amdgcn_readlane(incl, l) - n;
-        }
-        base += wave_last(incl);
-      }
-    }
-    if (l < 0) return {-1, 0, 0, 0, 0};
+  } else if (a.S <= kWave ? !plan_by_wave<1>(a, u, lane, s, ns, first, n) : !plan_by_wave<kPlanRegs>(a, u, lane, s, ns, first, n)) {
+    return {-1, 0, 0, 0, 0};
   }
   const int rem = wg - first * a.Hkv;
   g = __builtin_amdgcn_readfirstlane(quick_div(rem, n));
