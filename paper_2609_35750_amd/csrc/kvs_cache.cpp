@@ -135,10 +135,14 @@ int BlockManager::append(int seq, const int32_t* pos, int n, int32_t* slots, std
   return kOk;
 }
 
-void BlockManager::drop_block(int seq, int blk) {
+// at: where the caller's last block stood in the list, and where this one did; an eviction of consecutive positions
+// frees consecutive blocks, so the search for each ends where the last one did.
+void BlockManager::drop_block(int seq, int blk, size_t* at) {
   auto& bl = blocks_[seq];
   const bool tail = !bl.empty() && bl.back() == blk;
-  bl.erase(std::find(bl.begin(), bl.end(), blk));
+  const auto it = *at < bl.size() && bl[*at] == blk ? bl.begin() + *at : std::find(bl.begin(), bl.end(), blk);
+  *at = it - bl.begin();
+  bl.erase(it);
   free_.push_back(blk);
   if (tail) tail_fill_[seq] = bs_;   // the next append opens a new block
 }
@@ -163,6 +167,7 @@ int BlockManager::evict(int seq, const int32_t* pos, int n, int32_t* slots, std:
     }
     *s ^= kTaken;
   }
+  size_t at = 0;
   for (int i = 0; i < n; ++i) {
     const int p = pos[i];
     int* s = map.find(p);
@@ -171,7 +176,7 @@ int BlockManager::evict(int seq, const int32_t* pos, int n, int32_t* slots, std:
     map.count(p, -1);
     slots[i] = slot;
     const int blk = slot / bs_;
-    if (--live_[blk] == 0) drop_block(seq, blk);
+    if (--live_[blk] == 0) drop_block(seq, blk, &at);
   }
   return kOk;
 }

@@ -72,7 +72,7 @@ class BlockManager {
   int max_blocks() const { return mb_; }
 
  private:
-  void drop_block(int seq, int blk);
+  void drop_block(int seq, int blk, size_t* at);
 
   int nb_, bs_, ns_, mb_;
   std::vector<int> free_;                               // free block ids (LIFO)
