@@ -84,7 +84,7 @@ def _code_only(text):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("kvs_kernels.hip", "kvs_paged.hip", "kvs_device.h"):
+    for f in ("kvs_kernels.hip", "kvs_paged.hip", "kvs_device.h", "kvs_decode_plan.h"):
         with open(os.path.join(ROOT, "paper_2609_35750_amd", "csrc", f), encoding="utf-8") as fh:
             h.update(_code_only(fh.read()).encode())
     return h.hexdigest()[:16]

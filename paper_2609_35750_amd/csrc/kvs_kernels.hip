@@ -694,14 +694,15 @@ __global__ void __launch_bounds__(512) dq_kernel(RowArgs a) {
 // dK and dV accumulators (2 x 64 registers at D = 128 of a wave's 256), is
 // staged in LDS once per item.  At the item's end the two row halves are added
 // through the (then free) tile buffers: wave w < 4 stores dV, wave w + 4 dK.
-// Bound by the matrix cores (62% busy on the 16k trace) at the clock their power
-// leaves: each wave is one chain of S, dP, the exponentials, dV and dK, and two
-// waves a SIMD cover each other's.  A pair of waves that splits the products
-// instead (one S and dV, the other dP and dK of the same block, P through LDS in
-// 16 bits) is locked together by every step's barrier: 15% more cycles, 53% busy,
-// at a clock 8% higher.  That against this, us: 16k trace (32/8 heads, D = 128)
-// 1,994 -> 1,812, two of 4,097 406 -> 357, 24 of 100 to 1,500 (16/2) 138 -> 127,
-// 8,191 tokens (24/8, D = 64) 229 -> 207, 512 tokens (4/4, D = 64) 14.7 -> 14.0.
+// Bound by the matrix cores (busy 58% of the kernel's cycles on the 16k trace) at
+// the clock their power leaves: each wave is one chain of S, dP, the exponentials,
+// dV and dK, and two waves a SIMD cover each other's.  A pair of waves that splits
+// the products instead (one S and dV, the other dP and dK of the same block, P
+// through LDS in 16 bits) is locked together by every step's barrier: 17% more
+// cycles, 50% busy, at a higher clock.  That against this, kernel traces of one
+// run, us: 16k trace (32/8 heads, D = 128) 1,852 -> 1,711, two of 4,097 340 -> 318,
+// 24 of 100 to 1,500 (16/2) 135 -> 118, 8,191 tokens (24/8, D = 64) 208 -> 179, 512
+// tokens (4/4, D = 64) 14.9 -> 13.7.
 template <int D>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) dkdv_kernel(ColArgs a) {
   constexpr int KS = D / 16, DB = D / 32, PITCH = Lay<D>::PITCH, kHalf = kQStep * PITCH, kTile = 2 * kHalf;
@@ -1026,11 +1027,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 // later blocks stay whole.  All work items (whole blocks and parts) are then
 // listed longest first (counting sort on the step count).  One workgroup of
 // 1024 threads; block spans come from the 64-key tile statistics.
-// dK/dV time with parts of 64 row-steps only, cut beyond 128, and with these:
-// 24 traces of 100 to 1,500 tokens (16/2 heads, D = 128) 336 -> 141 us, two of
-// 4,097 (32/8) 450 -> 338 us, one of 8,191 (24/8, D = 64) 468 -> 198 us (with the
-// kernel's products split over pairs of waves; 127, 357 and 207 now).  Parts
-// of 1/2 and 1/4 share and a threshold of 2/3 or 4/5 share: within 5% of that.
+// dK/dV kernel with parts of 64 row-steps only, cut beyond 128, and with these
+// (kernel traces of one run, its products split over pairs of waves on both
+// sides): 24 traces of 100 to 1,500 tokens (16/2 heads, D = 128) 336 -> 139 us, two
+// of 4,097 (32/8) 462 -> 354, one of 8,191 (24/8, D = 64) 474 -> 217; plan and
+// reduce take 15 to 18 us of that back.  Parts of 1/2 and 1/4 share and a
+// threshold of 2/3 or 4/5 share: within 5%.
 __global__ void __launch_bounds__(1024) split_plan_kernel(const int2* __restrict__ kstats, const int* __restrict__ cu,
                                                           int B, int T, int ntok, int nkt, int G, int Hkv, int capE,
                                                           int grid, int nq, int* __restrict__ plan, int2* __restrict__ items,

@@ -271,12 +271,12 @@ __device__ __forceinline__ bool plan_by_wave(const DecodeArgs& a, int u, int lan
 // of the wave take part.  A sequence's workgroups are consecutive, its units
 // fastest, then the KV heads.
 __device__ __forceinline__ DecodeUnit decode_unit(const DecodeArgs& a, int wg, int lane, int& g) {
-  const int u = quick_div(wg, a.Hkv);
+  const int u = __builtin_amdgcn_readfirstlane(quick_div(wg, a.Hkv));
   g = wg - u * a.Hkv;
   if (a.plan == kOneUnit) return {u, slots_of(a, u), u, 1, 0};
   int s = 0, ns = 0, first = 0, n = 0;
   if (a.plan == kListed) {
-    const int4 m = a.unit_seq[__builtin_amdgcn_readfirstlane(u)];
+    const int4 m = a.unit_seq[u];
     s = m.x, ns = m.y, first = m.z, n = m.w;
     if (n == 0) return {-1, 0, 0, 0, 0};
   } else if (a.S <= kWave ? !plan_by_wave<1>(a, u, lane, s, ns, first, n) : !plan_by_wave<kPlanRegs>(a, u, lane, s, ns, first, n)) {
@@ -805,7 +805,7 @@ hipError_t launch_paged_decode(const PagedDecode& p) {
   a.part = (float*)p.ws;
   a.part_ml = (float2*)((char*)p.ws + round256(rows * p.D * sizeof(float)));
   a.seq_units = (int2*)((char*)a.part_ml + round256(rows * sizeof(float2)));
-  a.cut = (int*)a.seq_units;   // at most units - S cut sequences, and no more than S; S > 1 where they are listed
+  a.cut = (int*)a.seq_units;   // their number and no more than S first units: at most S + 1 of 2 S words
   a.unit_seq = (int4*)((char*)a.seq_units + round256((size_t)p.S * sizeof(int2)));
   a.scale_log2 = p.scale * 1.4426950408889634f;
   const dim3 grid((unsigned)((long long)a.units * p.Hkv));
