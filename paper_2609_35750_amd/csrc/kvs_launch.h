@@ -87,7 +87,7 @@ struct PagedDecode {
   hipStream_t stream;
 };
 // Slots of a host-held list as runs: |len| tokens from `tok` on, positions pos, pos + 1, ..., slots slot, slot + 1,
-// ... (or slot, slot - 1, ... for len < 0).  Passed by value: 2.5 KB of launch arguments.
+// ... (or slot, slot - 1, ... for len < 0).  Passed by value: 2 KB of launch arguments.
 struct SlotRun {
   int tok, slot, pos, len;
 };
@@ -95,36 +95,41 @@ constexpr int kMaxRuns = 128;
 struct SlotRuns {
   int n;
   SlotRun r[kMaxRuns];
-  int first[kMaxRuns];   // RunGrid::items > 0: workgroup the run begins with
 };
-// Grid of the run kernels, for per_tok items a token.  items = 0: workgroups x * 256 items of every run (y), in strides
-// of the grid.  Where runs of unequal length would leave more than half of those without any: items > 0, workgroups
-// first[i] to first[i + 1] - 1 are run i's, `items` of its items each (256, more beyond 65,535 workgroups).
-struct RunGrid {
-  unsigned x, y;
-  long long items;
+// How the run kernels share the runs' work, per_tok items a token.  Without a list: x workgroups for every run (y), in
+// strides of 256 x items.  Where runs of unequal length would leave more than kIdleGroups of those without any: run i
+// has workgroups first[i] to first[i + 1] - 1, of `items` items each (256, more beyond 65,535 workgroups).
+struct NoRunList {
+  static constexpr bool kListed = false;
 };
-inline RunGrid share_runs(SlotRuns* runs, long long per_tok) {
-  auto work = [&](int i) { return (runs->r[i].len < 0 ? -(long long)runs->r[i].len : runs->r[i].len) * per_tok; };
-  long long all = 0, longest = 0;
-  for (int i = 0; i < runs->n; ++i) {
+struct RunList {
+  static constexpr bool kListed = true;
+  long long items;   // 0: no list
+  int first[kMaxRuns];
+};
+constexpr int kIdleGroups = 4096;
+inline dim3 run_grid(const SlotRuns& runs, long long per_tok, RunList* list) {
+  auto work = [&](int i) { return (runs.r[i].len < 0 ? -(long long)runs.r[i].len : runs.r[i].len) * per_tok; };
+  long long all = 0, busy = 0, each = 0;   // items; workgroups of all runs, of the longest
+  for (int i = 0; i < runs.n; ++i) {
+    const long long groups = (work(i) + 255) / 256;
     all += work(i);
-    longest = work(i) > longest ? work(i) : longest;
+    busy += groups;
+    each = groups > each ? groups : each;
   }
-  const long long each = (longest + 255) / 256;
-  if (runs->n == 1 || each * runs->n <= 2 * ((all + 255) / 256 + runs->n))
-    return {(unsigned)(each < 4096 ? each : 4096), (unsigned)runs->n, 0};
-  const long long items = 256 * ((all + 256ll * 65535 - 1) / (256ll * 65535));
+  list->items = 0;
+  if (each * runs.n - busy <= kIdleGroups) return dim3((unsigned)(each < 4096 ? each : 4096), (unsigned)runs.n);
+  list->items = 256 * ((all + 256ll * 65535 - 1) / (256ll * 65535));
   unsigned wg = 0;
-  for (int i = 0; i < runs->n; ++i) {
-    runs->first[i] = (int)wg;
-    wg += (unsigned)((work(i) + items - 1) / items);
+  for (int i = 0; i < runs.n; ++i) {
+    list->first[i] = (int)wg;
+    wg += (unsigned)((work(i) + list->items - 1) / list->items);
   }
-  return {wg, 1, items};
+  return dim3(wg);
 }
-hipError_t launch_paged_append_runs(const void* kn, const void* vn, SlotRuns& runs, void* kc, void* vc,
+hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
                                     int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream);
-hipError_t launch_paged_evict_runs(SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
+hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream);
 size_t paged_ws_bytes(int S, int Hq, int Hkv, int max_blocks, int BS, int D);   // that the decode can use
 size_t paged_ws_least(int S, int Hq, int Hkv, int max_blocks, int BS, int D);   // that it needs
 hipError_t launch_paged_append(const void* kn, const void* vn, const int* pos, const int* slots, int n, void* kc,

@@ -63,39 +63,41 @@ __global__ void __launch_bounds__(256) paged_evict_kernel(const int* __restrict_
 // The same from slot lists the host holds, run by run: the slots a block manager
 // hands out lie in a few runs (a block's rows, and often blocks in a row), which
 // fit the launch's arguments, so nothing is uploaded.  Token i of a run: slot +
-// i * step, position + i.  Workgroups by run (share_runs): with the longest
+// i * step, position + i.  Workgroups by run (run_grid): with the longest
 // run's number for each, one long run beside many short ones, which is what a
 // fragmented free list hands out, starts up to 128 times what it needs.  4,096
 // tokens in a row and 100 by themselves (8 heads, D = 128): append 47 us that
-// way, 14 with a list of the runs' first workgroups (LIST); looking them up costs
-// 0.6 us of the 3 that 384 tokens in a few runs take, so those go by blockIdx.y.
-struct RunItems {
-  int run;
-  long long begin, end, step;   // of the workgroup's threads; end is not clamped to the run's
-};
-template <bool LIST>
-__device__ __forceinline__ RunItems run_items(const SlotRuns& runs, long long items) {
-  if (!LIST) return {(int)blockIdx.y, blockIdx.x * 256ll, LLONG_MAX, gridDim.x * 256ll};
+// way, 14 with a list of the runs' first workgroups (RunList).  Looking them up takes
+// 0.6 us, as long as some 4,000 idle workgroups; up to that the run is blockIdx.y.
+// The workgroup's run, the first of its items there, and how many of them it has.
+__device__ __forceinline__ int run_of(const SlotRuns&, const NoRunList&, long long& begin, long long& items) {
+  begin = blockIdx.x * 256ll;
+  items = LLONG_MAX;   // in strides of the grid
+  return blockIdx.y;
+}
+__device__ __forceinline__ int run_of(const SlotRuns& runs, const RunList& list, long long& begin, long long& items) {
   const int lane = threadIdx.x & 63;
   int k = -1;   // the last run that begins at or before this workgroup
 #pragma unroll
   for (int h = 0; h < kMaxRuns; h += kWave)
-    k += __builtin_popcountll(__ballot(h + lane < runs.n && runs.first[h + lane] <= (int)blockIdx.x));
+    k += __builtin_popcountll(__ballot(h + lane < runs.n && list.first[h + lane] <= (int)blockIdx.x));
   k = __builtin_amdgcn_readfirstlane(k);
-  const long long begin = (blockIdx.x - runs.first[k]) * items;
-  return {k, begin, begin + items, 256};
+  items = list.items;
+  begin = (blockIdx.x - list.first[k]) * items;
+  return k;
 }
 
-template <int D, bool LIST>
+template <int D, class L>
 __global__ void __launch_bounds__(256) paged_append_runs_kernel(const uint16_t* __restrict__ kn,
                                                                 const uint16_t* __restrict__ vn, SlotRuns runs,
-                                                                long long items, uint16_t* __restrict__ kc,
-                                                                uint16_t* __restrict__ vc, int* __restrict__ slot_pos,
-                                                                int num_slots, int Hkv, int BS) {
-  const RunItems it = run_items<LIST>(runs, items);
-  const SlotRun run = runs.r[it.run];
+                                                                uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
+                                                                int* __restrict__ slot_pos, int num_slots, int Hkv,
+                                                                int BS, L list) {
+  long long begin, items;
+  const SlotRun run = runs.r[run_of(runs, list, begin, items)];
   const long long per_tok = (long long)Hkv * (D / 8), chunks = (long long)(run.len < 0 ? -run.len : run.len) * per_tok;
-  for (long long c = it.begin + threadIdx.x; c < min(it.end, chunks); c += it.step) {
+  const long long end = items < chunks - begin ? begin + items : chunks, step = L::kListed ? 256 : gridDim.x * 256ll;
+  for (long long c = begin + threadIdx.x; c < end; c += step) {
     const long long i = c / per_tok, r = c - i * per_tok, src = ((long long)run.tok + i) * per_tok + r;
     const long long slot = run.slot + (run.len < 0 ? -i : i);
     if (slot < 0 || slot >= num_slots) continue;
@@ -107,14 +109,14 @@ __global__ void __launch_bounds__(256) paged_append_runs_kernel(const uint16_t* 
   }
 }
 
-template <bool LIST>
-__global__ void __launch_bounds__(256) paged_evict_runs_kernel(SlotRuns runs, long long items,
-                                                               int* __restrict__ slot_pos, int num_slots) {
-  const RunItems it = run_items<LIST>(runs, items);
-  const SlotRun run = runs.r[it.run];
-  const unsigned n = (unsigned)min(it.end, (long long)(run.len < 0 ? -run.len : run.len));
-  for (unsigned i = (unsigned)it.begin + threadIdx.x; i < n; i += (unsigned)it.step) {
-    const long long slot = run.slot + (run.len < 0 ? -(long long)i : (long long)i);
+template <class L>
+__global__ void __launch_bounds__(256) paged_evict_runs_kernel(SlotRuns runs, int* __restrict__ slot_pos,
+                                                               int num_slots, L list) {
+  long long begin, items;
+  const SlotRun run = runs.r[run_of(runs, list, begin, items)];
+  const int n = run.len < 0 ? -run.len : run.len, end = items < n - begin ? (int)(begin + items) : n;
+  for (int i = (int)begin + threadIdx.x; i < end; i += L::kListed ? 256 : gridDim.x * 256) {
+    const long long slot = (long long)run.slot + (run.len < 0 ? -i : i);
     if (slot >= 0 && slot < num_slots) slot_pos[slot] = -1;
   }
 }
@@ -660,16 +662,15 @@ template __global__ void paged_append_kernel<64>(const uint16_t*, const uint16_t
                                                  uint16_t*, uint16_t*, int*, int, int, int);
 template __global__ void paged_append_kernel<128>(const uint16_t*, const uint16_t*, const int*, const int*, int,
                                                   uint16_t*, uint16_t*, int*, int, int, int);
-#define KVS_APPEND_RUNS(DD, LL)                                                                                       \
-  template __global__ void paged_append_runs_kernel<DD, LL>(const uint16_t*, const uint16_t*, SlotRuns, long long, \
-                                                            uint16_t*, uint16_t*, int*, int, int, int)
-KVS_APPEND_RUNS(64, false);
-KVS_APPEND_RUNS(64, true);
-KVS_APPEND_RUNS(128, false);
-KVS_APPEND_RUNS(128, true);
-#undef KVS_APPEND_RUNS
-template __global__ void paged_evict_runs_kernel<false>(SlotRuns, long long, int*, int);
-template __global__ void paged_evict_runs_kernel<true>(SlotRuns, long long, int*, int);
+#define KVS_RUNS(LL)                                                                                               \
+  template __global__ void paged_append_runs_kernel<64, LL>(const uint16_t*, const uint16_t*, SlotRuns, uint16_t*, \
+                                                            uint16_t*, int*, int, int, int, LL);                   \
+  template __global__ void paged_append_runs_kernel<128, LL>(const uint16_t*, const uint16_t*, SlotRuns, uint16_t*, \
+                                                             uint16_t*, int*, int, int, int, LL);                  \
+  template __global__ void paged_evict_runs_kernel<LL>(SlotRuns, int*, int, LL)
+KVS_RUNS(NoRunList);
+KVS_RUNS(RunList);
+#undef KVS_RUNS
 template __global__ void paged_decode_kernel<64>(DecodeArgs);
 template __global__ void paged_decode_kernel<128>(DecodeArgs);
 template __global__ void paged_combine_kernel<64, 1, false>(DecodeArgs);
@@ -682,20 +683,30 @@ template __global__ void paged_combine_kernel<64, 4, true>(DecodeArgs);
 template __global__ void paged_combine_kernel<128, 4, true>(DecodeArgs);
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_paged_append_runs(const void* kn, const void* vn, SlotRuns& runs, void* kc, void* vc, int* slot_pos,
-                                    int num_slots, int BS, int Hkv, int D, hipStream_t stream) {
-  const RunGrid g = share_runs(&runs, (long long)Hkv * (D / 8));
-  const auto kernel = D == 128 ? (g.items ? paged_append_runs_kernel<128, true> : paged_append_runs_kernel<128, false>)
-                               : (g.items ? paged_append_runs_kernel<64, true> : paged_append_runs_kernel<64, false>);
-  hipLaunchKernelGGL(kernel, dim3(g.x, g.y), dim3(256), 0, stream, (const uint16_t*)kn, (const uint16_t*)vn, runs,
-                     g.items, (uint16_t*)kc, (uint16_t*)vc, slot_pos, num_slots, Hkv, BS);
+template <class L>
+static void launch_append_runs(dim3 grid, const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
+                               int* slot_pos, int num_slots, int BS, int Hkv, int D, const L& list, hipStream_t stream) {
+  const auto kernel = D == 128 ? paged_append_runs_kernel<128, L> : paged_append_runs_kernel<64, L>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, (const uint16_t*)kn, (const uint16_t*)vn, runs, (uint16_t*)kc,
+                     (uint16_t*)vc, slot_pos, num_slots, Hkv, BS, list);
+}
+hipError_t launch_paged_append_runs(const void* kn, const void* vn, const SlotRuns& runs, void* kc, void* vc,
+                                    int* slot_pos, int num_slots, int BS, int Hkv, int D, hipStream_t stream) {
+  RunList list;
+  const dim3 grid = run_grid(runs, (long long)Hkv * (D / 8), &list);
+  if (list.items) launch_append_runs(grid, kn, vn, runs, kc, vc, slot_pos, num_slots, BS, Hkv, D, list, stream);
+  else launch_append_runs(grid, kn, vn, runs, kc, vc, slot_pos, num_slots, BS, Hkv, D, NoRunList{}, stream);
   return hipGetLastError();
 }
 
-hipError_t launch_paged_evict_runs(SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream) {
-  const RunGrid g = share_runs(&runs, 1);
-  const auto kernel = g.items ? paged_evict_runs_kernel<true> : paged_evict_runs_kernel<false>;
-  hipLaunchKernelGGL(kernel, dim3(g.x, g.y), dim3(256), 0, stream, runs, g.items, slot_pos, num_slots);
+hipError_t launch_paged_evict_runs(const SlotRuns& runs, int* slot_pos, int num_slots, hipStream_t stream) {
+  RunList list;
+  const dim3 grid = run_grid(runs, 1, &list);
+  if (list.items)
+    hipLaunchKernelGGL(paged_evict_runs_kernel<RunList>, grid, dim3(256), 0, stream, runs, slot_pos, num_slots, list);
+  else
+    hipLaunchKernelGGL(paged_evict_runs_kernel<NoRunList>, grid, dim3(256), 0, stream, runs, slot_pos, num_slots,
+                       NoRunList{});
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
-// Host build of two launch grids.  Slot runs (share_runs): every item of every run
+// Host build of two launch grids.  Slot runs (run_grid): every item of every run
 // belongs to exactly one workgroup, found as the kernels find it (blockIdx.y, or
 // the last run that begins at or before it), and there are no more workgroups
-// than twice the runs' work asks for, however unequal the runs are.  And the
+// than the runs' work asks for and kIdleGroups, however unequal the runs are.  And the
 // grid of the backward's preprocess: it takes every number of rows that fits a
 // launch by itself, with the key-tile statistics only where they fit as well.
 // Prints "ok" and exits 0, or names the first failure.
@@ -13,7 +13,8 @@
 #include "kvs_launch.h"
 
 static int check(kvs::SlotRuns& runs, long long per_tok) {
-  const kvs::RunGrid g = kvs::share_runs(&runs, per_tok);
+  kvs::RunList list;
+  const dim3 g = kvs::run_grid(runs, per_tok, &list);
   auto work = [&](int i) { return std::abs((long long)runs.r[i].len) * per_tok; };
   long long all = 0, need = 0, given = 0;
   for (int i = 0; i < runs.n; ++i) {
@@ -21,11 +22,11 @@ static int check(kvs::SlotRuns& runs, long long per_tok) {
     need += (work(i) + 255) / 256;
   }
   const long long grid = (long long)g.x * g.y;
-  if (g.x < 1 || g.y < 1 || grid > 2 * need + 2 * runs.n || grid > 65535ll * 9 + runs.n) {
-    std::printf("%d runs, %lld items: %u x %u workgroups of %lld\n", runs.n, all, g.x, g.y, g.items);
+  if (g.x < 1 || g.y < 1 || grid > need + kvs::kIdleGroups || (list.items && grid > 65535ll + runs.n)) {
+    std::printf("%d runs, %lld items: %u x %u workgroups of %lld\n", runs.n, all, g.x, g.y, list.items);
     return 1;
   }
-  if (g.items == 0) {   // strides of the grid: every run has its workgroups
+  if (list.items == 0) {   // strides of the grid: every run has its workgroups
     if (g.y != (unsigned)runs.n) {
       std::printf("%d runs, %u rows of workgroups\n", runs.n, g.y);
       return 1;
@@ -35,15 +36,15 @@ static int check(kvs::SlotRuns& runs, long long per_tok) {
   int last = -1;
   for (unsigned wg = 0; wg < g.x; ++wg) {
     int k = 0;
-    for (int i = 0; i < runs.n; ++i) k += runs.first[i] <= (int)wg;
+    for (int i = 0; i < runs.n; ++i) k += list.first[i] <= (int)wg;
     --k;
-    const long long c0 = (wg - runs.first[k]) * g.items;
+    const long long c0 = (wg - list.first[k]) * list.items;
     if (k < last || c0 >= work(k)) {
       std::printf("workgroup %u of %u: run %d, item %lld of %lld\n", wg, g.x, k, c0, work(k));
       return 1;
     }
     last = k;
-    given += std::min(g.items, work(k) - c0);
+    given += std::min(list.items, work(k) - c0);
   }
   if (given != all) {
     std::printf("%lld of %lld items given out\n", given, all);

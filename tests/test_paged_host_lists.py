@@ -194,3 +194,40 @@ def test_host_lists_are_not_captured():
         torch.cuda.synchronize()
     assert count.item() == 3 and (k == 0).all() and (sp == -1).all()
     assert both() == (kvs.KVS_OK, kvs.KVS_OK)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("down", [False, True])
+def test_one_long_run_beside_short_ones(down):
+    """So unequal that appends and evictions both share the runs' work by a list of first workgroups."""
+    from paper_2609_35750_amd import kvs, paged
+
+    dev, lib = torch.device("cuda:0"), kvs.lib
+    Hkv, D, bs, nb = 1, 64, 16, 1024
+    slots = np.asarray([13000 + 2 * i for i in range(60)] + list(range(12000)) + [13400 - 2 * i for i in range(60)],
+                       dtype=np.int32)
+    if down:
+        slots = np.ascontiguousarray(slots[::-1])
+    n = slots.size
+    pos = np.arange(7, 7 + n, dtype=np.int32)
+    kn, vn = (inputs.randn_bf16((n, Hkv, D), 50 + i).to(dev) for i in range(2))
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)   # noqa: E731
+    stream = torch.cuda.current_stream().cuda_stream
+    caches = []
+    for host in (True, False):
+        k, v = (torch.zeros((nb, Hkv, bs, D), dtype=torch.bfloat16, device=dev) for _ in range(2))
+        sp = torch.full((nb * bs,), -1, dtype=torch.int32, device=dev)
+        if host:
+            assert lib.kvs_paged_append_host(kn.data_ptr(), vn.data_ptr(), p(pos), p(slots), n, k.data_ptr(),
+                                             v.data_ptr(), sp.data_ptr(), nb, bs, Hkv, D, stream) == kvs.KVS_OK
+        else:
+            paged.kvs_paged_append(kn, vn, torch.from_numpy(pos).to(dev), torch.from_numpy(slots).to(dev), k, v, sp, bs)
+        full = sp.clone()
+        gone = np.ascontiguousarray(slots[30:])
+        if host:
+            assert lib.kvs_paged_evict_host(p(gone), gone.size, sp.data_ptr(), nb, bs, stream) == kvs.KVS_OK
+        else:
+            paged.kvs_paged_evict(torch.from_numpy(gone).to(dev), sp, nb, bs)
+        caches.append((k.view(torch.int16), v.view(torch.int16), full, sp))
+    for a, b in zip(*caches):
+        assert torch.equal(a, b)
