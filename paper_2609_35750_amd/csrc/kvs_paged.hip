@@ -198,7 +198,7 @@ struct GatherStager {
 // load, and the merge walks the cut sequences only.
 // Cutting every sequence into the same number of splits instead: 24 rollouts
 // of 200 to 9,000 entries (D = 64, 195 MB) 51.8 -> 39.9 us, 40 of 500 to 8,000
-// (D = 128, 674 MB) 162 -> 119 us, one of 16,000 beside 63 of 200 379 -> 28 us
+// (D = 128, 674 MB) 162 -> 119 us, one of 16,000 beside 63 of 200 378 -> 36 us
 // (these with the streamed gather).
 struct DecodeUnit {
   int s, nslots, first, n, chunk;   // sequence, its slots, its first unit, its units, this one among them
